@@ -173,7 +173,10 @@ sivf_status sivf_tune_search(sivf_index *ix, int64_t nq, const float *q, int32_t
  * results -- when dim <= 256 and slab_capacity >= 4; reduced
  * precision: 16), 2^chunk_shift = positions per
  * work item (6..31), persistent = 0 (one wave per item) or 1 (resident
- * waves).  SIVF_ERR_ARG for other values.  Applies to later calls. */
+ * waves).  SIVF_ERR_ARG for other values.  Applies to later calls.  Until a
+ * schedule is set or tuned, a search of few (query, list) pairs per list takes
+ * 2 or 4 queries per work item instead of the default.  Under every schedule a
+ * batch too small to fill the chip takes shorter work items. */
 sivf_status sivf_set_search_schedule(sivf_index *ix, int32_t tile, int32_t chunk_shift, int32_t persistent);
 
 /* Schedule of the k > 64 pass (fp32 storage).  Under the certified scan

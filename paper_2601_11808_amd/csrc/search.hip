@@ -103,6 +103,28 @@ __device__ __forceinline__ int list_chunks(int len, int sh) {
     return len > 0 ? (int)(((int64_t)len + (1ll << sh) - 1) >> sh) : 0;
 }
 
+// Chunk of a search whose scan costs `cost` (list positions x query tiles of T):
+// log2 of the positions per work item, at most sh0.  FILL_ITEMS work items
+// fill the chip once (12 waves on each of 256 CUs); a batch with fewer than that at
+// sh0 gets shorter chunks.  VALU scans (T < 16) have no start-up worth keeping
+// long chunks for: at least FILL_ITEMS items, down to 2 steps of 64 positions
+// (1 query, 32 lists of about 2,500: 333 us in 32 items, 16 in 640).  The
+// matrix-core scans pay for every work item's cold start (no threshold yet: a
+// bisection, and the exact distances of the first candidates) about what eight
+// steps cost: at most half of FILL_ITEMS items, of four steps or more
+// (3,277 queries x 6 lists of 1,000 x 32 values: 260 us unsplit, 322 us in chunks
+// of 256).  A larger batch on them gets chunks of 2^13, while those are at most
+// 8 FILL_ITEMS: a very long list otherwise ends long after the others (3,854
+// queries with k up to 100 on lists of 400 to 300,000: 5.4 ms at 2^14, 4.5 ms at
+// 2^13).
+constexpr int FILL_ITEMS = 3072;
+__device__ __forceinline__ int plan_shift(long long cost, int sh0, int T) {
+    auto flog2 = [](long long v) { return v <= 1 ? 0 : 63 - __clzll(v); };
+    const int fill = flog2(cost / FILL_ITEMS);
+    const int s = T < 16 ? max(fill, 7) : max(min(max(fill + 2, 8), 13), flog2(cost / (8 * FILL_ITEMS)) + 1);
+    return min(s, sh0);
+}
+
 // One block plans the whole search:
 //  1. snapshot every list's length (the scan reads only these entries; a
 //     second pass of the same search keeps the first pass's snapshot) and
@@ -140,7 +162,14 @@ __global__ __launch_bounds__(1024) void k_inv_plan(Dev S, int T, int sh0, int64_
         carry_p += tp;
     }
     // each thread re-reads only the lists it wrote above
-    int sh = sh0;
+    // total scan cost (list positions x query tiles)
+    long long wsum = 0, wdummy = 0;
+    for (int l = threadIdx.x; l < S.nlist; l += 1024) {
+        const int qc = S.l_qcs[l];
+        if (qc > 0) wsum += (long long)cdiv_s(qc, T) * S.l_snap[l];
+    }
+    block_sum2(wsum, wdummy, sred);
+    int sh = plan_shift(wsum, sh0, T);
     for (;;) {
         long long slots = 0, items = 0;
         for (int l = threadIdx.x; l < S.nlist; l += 1024) {
@@ -153,13 +182,7 @@ __global__ __launch_bounds__(1024) void k_inv_plan(Dev S, int T, int sh0, int64_
         if ((slots <= slot_cap && items <= item_cap) || sh >= 31) break;   // sh = 31: one chunk per list
         sh++;
     }
-    // total scan cost first, so that each list can tell which XCD boundaries fall in it
-    long long wsum = 0, wdummy = 0;
-    for (int l = threadIdx.x; l < S.nlist; l += 1024) {
-        const int qc = S.l_qcs[l];
-        if (qc > 0) wsum += (long long)cdiv_s(qc, T) * S.l_snap[l];
-    }
-    block_sum2(wsum, wdummy, sred);
+    // the total cost is known, so each list can tell which XCD boundaries fall in it
     if (threadIdx.x < 9) sxb[threadIdx.x] = -1;
     __syncthreads();
     int carry_s = 0, carry_i = 0;
@@ -478,7 +501,7 @@ __device__ __forceinline__ uint32_t key_hi(float v) {
         const float4 *xp = S.data + (int64_t)slab * dp4 * C + slot;                              \
         float acc[T];                                                                            \
         _Pragma("unroll") for (int t = 0; t < T; t++) acc[t] = 0.f;                              \
-        _Pragma("unroll 2") for (int c = 0; c < dp4; c++) {                                      \
+        _Pragma("unroll UNR") for (int c = 0; c < dp4; c++) {                                    \
             const float4 xv = xp[(int64_t)c * C];                                                \
             _Pragma("unroll") for (int t = 0; t < T; t++) {                                      \
                 const float4 qv = QV(t, c);                                                      \
@@ -520,6 +543,12 @@ __device__ __forceinline__ int query_k(const int32_t *kpq, int k, int qi) {
     return kq < 0 ? 0 : (kq > k ? k : kq);
 }
 
+// Dimension chunks in flight per lane.  The fewer queries share a chunk, the
+// less VALU work covers its load, and the more registers are free for loads: T x
+// unroll = 16.  1,000 queries on 96-entry tiles of 960-value rows, T = 4: 335 us
+// with two chunks in flight, 267 with four.
+constexpr int scan_unroll(int T) { return 16 / T; }
+
 // Queries come straight from the caller's rows with wave-uniform addresses,
 // so the compiler reads them through the scalar cache into SGPRs and every
 // VALU op takes its query operand from an SGPR (no LDS traffic).  Needs
@@ -537,6 +566,7 @@ __global__ __launch_bounds__(64) void k_scan_sq(Dev S, const int32_t *__restrict
     const int dp4 = S.dp4, C = S.C, sh = S.ctl[CTL_CHUNK];
     SIVF_ITEM_LOOP_BEGIN
     SIVF_ITEM_DECODE(T)
+    constexpr int UNR = scan_unroll(T);
     const float4 *qrow[T];
     TopK<T, WIDE> K;
 #pragma unroll
@@ -569,6 +599,7 @@ __global__ __launch_bounds__(64) void k_scan(Dev S, const int32_t *__restrict__ 
     const int dp4 = S.dp4, C = S.C, d = S.d, sh = S.ctl[CTL_CHUNK];
     SIVF_ITEM_LOOP_BEGIN
     SIVF_ITEM_DECODE(T)
+    constexpr int UNR = scan_unroll(T);
     TopK<T, WIDE> K;
     __syncthreads();
     for (int t = 0; t < T; t++) {
@@ -597,117 +628,126 @@ __global__ __launch_bounds__(64) void k_scan(Dev S, const int32_t *__restrict__ 
 
 #undef SIVF_SCAN_RANGE
 
-// A pair whose list was split into chunks has one partial list per chunk:
-// merge them into the first.  One thread per pair finds the split ones; the
-// wave merges them one at a time.
-template <bool WIDE>
-__global__ __launch_bounds__(256) void k_chunk_merge(Dev S, int npairs, const int32_t *__restrict__ probes,
-                                                     const int32_t *__restrict__ pair_rank,
-                                                     uint64_t *__restrict__ partials, int kcap) {
-    const int p = blockIdx.x * 256 + threadIdx.x, lane = lane_id();
-    const int sh = S.ctl[CTL_CHUNK];
-    const int l = (p < npairs && pair_rank[p] >= 0) ? probes[p] : -1;   // pairs of this pass only
-    const int nc = l >= 0 ? list_chunks(S.l_snap[l], sh) : 0;
-    const int64_t slot = nc > 1 ? (int64_t)S.l_pbase[l] + (int64_t)pair_rank[p] * nc : 0;
-    uint64_t mask = ballot(nc > 1);
-    while (mask) {
-        const int src = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        const int m = __shfl(nc, src);
-        const int64_t s0 = ((int64_t)__shfl((int)(slot >> 32), src) << 32) | (uint32_t)__shfl((int)slot, src);
-        uint64_t *dst = partials + s0 * kcap;
-        uint64_t a = lane < kcap ? dst[lane] : ~0ull;
-        uint64_t a2 = (WIDE && lane + 64 < kcap) ? dst[64 + lane] : ~0ull;
-        for (int c = 1; c < m; c++) {
-            const uint64_t *src_c = dst + (int64_t)c * kcap;
-            const uint64_t b0 = lane < kcap ? src_c[lane] : ~0ull;
-            if (WIDE) {
-                merge128_with(a, a2, b0);
-                const uint64_t b1 = lane + 64 < kcap ? src_c[64 + lane] : ~0ull;
-                merge128_with(a, a2, b1);
-            } else {
-                a = merge_sorted_with(a, b0);
-            }
-        }
-        if (lane < kcap) dst[lane] = a;
-        if (WIDE && lane + 64 < kcap) dst[64 + lane] = a2;
-    }
-}
-
-// One wave per query: repeatedly take the smallest head among the query's
-// probe partial lists (each sorted, kcap long; a split list's chunks were
-// merged into its first slot).  k: the call's k; each query keeps kmul * (its
-// k) results, at most out_stride (the row stride of dist / labels, <= 128).
-// prior (or NULL): one more sorted source per query, prior_stride keys (~0
-// padded) -- the host tier's results; keys_out (or NULL): write the sorted
-// keys there (stride out_stride, ~0 padded) instead of dist / labels.
+// The best keys of each query's partial lists (one per probe and chunk,
+// sorted, kcap long), by WPQ waves per query.  The lists are numbered probe after
+// probe, 64 probes at a time; each lane takes one list of a round of 64, reads it
+// four keys at a time and leaves it at the first key above the bound; keys up to
+// the bound are queued in LDS and merged 64 at a time into the sorted result
+// (bitonic network), whose kq-th key is the new bound.  The bound starts at the
+// value the scan's work items published for the query (gthr; the kq best keys are
+// at or below it), so few keys of most lists are read at all.  What bounds it is the
+// chain of dependent reads, one or two per round of lists, not kq rounds of a
+// k-way merge: 40 keys of 40 lists per query (477 queries) took 38 us with one
+// key per round and takes 14.  The waves of a query take its rounds in turn
+// and the first merges their results: WPQ = 4 where the queries alone leave
+// the chip idle (few queries, their lists split into many chunks).
+// k: the call's k; each query keeps kmul * (its k) results, at most out_stride
+// (the row stride of dist / labels, <= 128).  prior (or NULL): one more sorted
+// source per query, prior_stride keys (~0 padded) -- the host tier's results;
+// keys_out (or NULL): write the sorted keys there (stride out_stride, ~0
+// padded) instead of dist / labels.
+constexpr int MG_BUF = 64 + 4 * 64;   // a round adds at most 4 keys per lane to fewer than 64 waiting ones
+template <bool WIDE, int WPQ>
 __global__ __launch_bounds__(256) void k_merge(Dev S, int nq, int np_stride, const int32_t *__restrict__ probes,
                                                const int32_t *__restrict__ pair_rank,
                                                const uint64_t *__restrict__ partials, int kcap, int out_stride,
                                                int k, int kmul, const int32_t *__restrict__ kpq,
                                                float *__restrict__ dist, int64_t *__restrict__ labels, KClass cls,
+                                               const uint32_t *__restrict__ gthr,
                                                const uint64_t *__restrict__ prior, int prior_stride,
                                                uint64_t *__restrict__ keys_out) {
-    __shared__ unsigned char heads[4][1024];
+    __shared__ uint64_t sbuf[4][MG_BUF];
     const int w = threadIdx.x >> 6, lane = lane_id();
-    const int qi = blockIdx.x * 4 + w;
-    if (qi >= nq || !in_class(cls, qi)) return;   // a query of another pass: its results come from that one
+    const int sub = w % WPQ;   // this wave's turn among the query's waves
+    const int qi = blockIdx.x * (4 / WPQ) + w / WPQ;
+    // a query of another pass: its results come from that one (a query's waves leave together, and with
+    // WPQ > 1 they are the whole block)
+    if (qi >= nq || !in_class(cls, qi)) return;
     const int sh = S.ctl[CTL_CHUNK];
     int kq = kpq ? kpq[qi] : k;
     kq = kq < 0 ? 0 : (kq > k ? k : kq);
     kq = min(kq * kmul, out_stride);
-    const int32_t *prow = probes + (int64_t)qi * np_stride;
-    const int32_t *rrow = pair_rank + (int64_t)qi * np_stride;
-    auto head_key = [&](int p) -> uint64_t {
-        const int l = prow[p];
-        if (l < 0) return ~0ull;
-        const int len = S.l_snap[l];
-        if (len == 0) return ~0ull;
-        const int h = heads[w][p];
-        const int64_t slot = (int64_t)S.l_pbase[l] + (int64_t)rrow[p] * list_chunks(len, sh);
-        return h < kcap ? partials[slot * kcap + h] : ~0ull;
-    };
-    uint64_t best = ~0ull;
-    int bestp = -1;
-    for (int p = lane; p < np_stride; p += 64) {
-        heads[w][p] = 0;
-        const uint64_t kk = head_key(p);
-        if (kk < best) {
-            best = kk;
-            bestp = p;
-        }
-    }
+    uint64_t *buf = sbuf[w];
     uint64_t res = ~0ull, res2 = ~0ull;   // result r sits in lane r (r < 64) or lane r - 64 of res2
-    const uint64_t *prow_k = prior ? prior + (int64_t)qi * prior_stride : nullptr;
-    int ph = 0;   // next key of the prior source (wave-uniform)
-    uint64_t pv = prow_k ? prow_k[0] : ~0ull;
-    for (int r = 0; r < kq; r++) {
-        uint64_t m = best;
+    // keys above the bound are not among the kq best
+    uint64_t bound = gthr ? ((uint64_t)gthr[qi] << 32) | 0xFFFFFFFFull : ~0ull;
+    auto take = [&](uint64_t b) {   // 64 more keys (~0: none)
+        if (WIDE) merge128_with(res, res2, b);
+        else res = merge_sorted_with(res, b);
+        const uint64_t kth = (WIDE && kq > 64) ? readlane_u64(res2, kq - 65) : readlane_u64(res, kq - 1);
+        bound = kth < bound ? kth : bound;
+    };
+    if (kq > 0) {
+        if (prior && sub == 0) {
+            const uint64_t *pr = prior + (int64_t)qi * prior_stride;
+            for (int i = 0; i < prior_stride; i += 64) take(i + lane < prior_stride ? pr[i + lane] : ~0ull);
+        }
+        const int32_t *prow = probes + (int64_t)qi * np_stride;
+        const int32_t *rrow = pair_rank + (int64_t)qi * np_stride;
+        int nb = 0;      // keys waiting in buf (wave-uniform)
+        int round = 0;
+        for (int p0 = 0; p0 < np_stride; p0 += 64) {
+            const int p = p0 + lane;
+            const int l = p < np_stride ? prow[p] : -1;
+            const int nc = l >= 0 ? list_chunks(S.l_snap[l], sh) : 0;
+            const int64_t slot = nc > 0 ? (int64_t)S.l_pbase[l] + (int64_t)rrow[p] * nc : 0;
+            const int incl = wave_incl_scan_dpp(nc);
+            const int total = readlane_i(incl, 63), excl = incl - nc;
+            for (int s0 = 0; s0 < total; s0 += 64) {
+                if (WPQ > 1 && (round++ % WPQ) != sub) continue;
+                // list s0 + lane: its probe is the last lane whose exclusive sum is at most it (empty
+                // probes share their sum with the next one)
+                const int s = s0 + lane;
+                int at = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const uint64_t u = shfl_xor_u64(m, o);
-            m = u < m ? u : m;
-        }
-        if (pv < m) {   // the prior source's head is smallest (keys are distinct)
-            if (lane == r) res = pv;
-            if (lane + 64 == r) res2 = pv;
-            ph++;
-            pv = ph < prior_stride ? prow_k[ph] : ~0ull;
-            continue;
-        }
-        if (m == ~0ull) break;
-        if (lane == r) res = m;
-        if (lane + 64 == r) res2 = m;
-        if (best == m) {
-            heads[w][bestp]++;
-            best = ~0ull;
-            bestp = -1;
-            for (int p = lane; p < np_stride; p += 64) {
-                const uint64_t kk = head_key(p);
-                if (kk < best) {
-                    best = kk;
-                    bestp = p;
+                for (int step = 32; step > 0; step >>= 1) {
+                    const int e = __shfl(excl, at + step);
+                    if (e <= s) at += step;
                 }
+                const int64_t base = ((int64_t)__shfl((int)(slot >> 32), at) << 32) | (uint32_t)__shfl((int)slot, at);
+                const uint64_t *src = partials + (base + (s - __shfl(excl, at))) * kcap;
+                bool open = s < total;
+                int j = 0;   // next key
+                while (ballot(open)) {
+                    uint64_t v[4] = {~0ull, ~0ull, ~0ull, ~0ull};
+                    if (open) {   // kcap is a multiple of 16: four keys, 32-byte aligned
+                        const ulonglong2 a = *reinterpret_cast<const ulonglong2 *>(src + j);
+                        const ulonglong2 b = *reinterpret_cast<const ulonglong2 *>(src + j + 2);
+                        v[0] = a.x;
+                        v[1] = a.y;
+                        v[2] = b.x;
+                        v[3] = b.y;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const bool pass = v[i] <= bound && v[i] != ~0ull;
+                        const uint64_t m = ballot(pass);
+                        if (pass) buf[nb + (int)__builtin_popcountll(m & lanemask_lt())] = v[i];
+                        nb += (int)__builtin_popcountll(m);
+                    }
+                    j += 4;
+                    if (v[3] > bound || v[3] == ~0ull || j >= kcap) open = false;
+                    __builtin_amdgcn_wave_barrier();
+                    while (nb >= 64) {
+                        nb -= 64;
+                        take(buf[nb + lane]);
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            }
+        }
+        if (nb > 0) take(lane < nb ? buf[lane] : ~0ull);
+    }
+    if (WPQ > 1) {   // the other waves' results join the first's
+        __builtin_amdgcn_wave_barrier();
+        buf[lane] = res;
+        if (WIDE) buf[64 + lane] = res2;
+        __syncthreads();
+        if (sub != 0) return;
+        if (kq > 0) {
+            for (int o = 1; o < WPQ; o++) {
+                take(sbuf[w + o][lane]);
+                if (WIDE) take(sbuf[w + o][64 + lane]);
             }
         }
     }
@@ -736,6 +776,27 @@ __global__ __launch_bounds__(256) void k_merge(Dev S, int nq, int np_stride, con
 int default_tile(int storage, int d, int C, int kcap) {
     if (storage != 0 || cert_ok(storage, d, C, kcap)) return 16;
     return d <= 1024 ? 8 : 4;
+}
+
+// Queries per work item of a search without a schedule of the caller's own, by
+// the pairs per list (each list is probed by about that many of the batch's
+// queries).  A tile of 16 on the matrix cores costs the same for one query as for
+// 16, and its threshold and exact recomputation start cold in every work item;
+// the VALU scan reads a list once per 2 or 4 queries.  Scan times in us at
+// 2, 4 and 16 queries per tile (1M x 128, 1,024 lists, 32 probes): 1 query
+// 16, 20, 40; 64 queries (2 pairs per list) 85, 90, 422; 200 (6 per list) -, 188,
+// 388; 500 (16 per list) -, 435, 413; 1,000 (31 per list) -, 699, 520.  On
+// 200k x 128 with 6 pairs per list 57, 62, 141.  For the pass of queries with k > 64
+// the matrix-core scan has to insert up to 128 keys per query and work item
+// one at a time, and pays off later (skewed 5M x 128, a third of the queries
+// at k = 100: 187 pairs per list 3.4 against 6.2 ms, 2,000 per list 28 against
+// 20 ms).  Wide rows (no matrix-core scan) take 4 rather than 8: 267 against
+// 374 us at 31 pairs per list of 960 values, 776 against 970 at 125.
+int auto_tile(const Dev &S, int64_t npairs, bool deep) {
+    if (S.storage != 0) return 16;
+    if (npairs <= 6ll * S.nlist) return 2;
+    if (S.tile != 16 || npairs <= (deep ? 400ll : 16ll) * S.nlist) return 4;
+    return 16;
 }
 
 int search_tile(const Dev &S) { return S.tile; }
@@ -1475,15 +1536,16 @@ __global__ __launch_bounds__(256) void k_rerank(Dev S, int nq, const float *__re
 }
 
 // Work items of a call without splitting: tiles of T pairs per list.  The
-// plan may split long lists until the items reach twice this (or the
-// buffer); the dispatch grid stays at this size.
+// plan may split long lists until the items reach twice this, or twice what
+// fills the chip (or the buffer); the dispatch grid covers that bound.
 static int64_t items_unsplit(const Dev &S, int npairs) {
     const int T = search_tile(S);
     return (npairs + T - 1) / T + (npairs < S.nlist ? npairs : S.nlist);
 }
 
 static int64_t item_limit(const Dev &S, const SearchBufs &W, int npairs) {
-    const int64_t lim = 2 * items_unsplit(S, npairs);
+    int64_t lim = 2 * items_unsplit(S, npairs);
+    lim = lim > 2 * FILL_ITEMS ? lim : 2 * FILL_ITEMS;   // room to split the lists of a small batch
     return lim < W.item_cap ? lim : W.item_cap;
 }
 
@@ -1638,10 +1700,12 @@ void launch_search_scan(hipStream_t st, const Dev &S, const SearchBufs &W, int n
         return;
     }
     if (kcap > 64) {
-        if (T == 8) launch_scan_t<8, true>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        if (T == 2) launch_scan_p<2, true, false>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        else if (T == 8) launch_scan_t<8, true>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
         else launch_scan_t<4, true>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
     } else {
-        if (T == 8) launch_scan_t<8, false>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        if (T == 2) launch_scan_p<2, false, false>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        else if (T == 8) launch_scan_t<8, false>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
         else launch_scan_t<4, false>(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
     }
 }
@@ -1650,17 +1714,19 @@ void launch_search_merge(hipStream_t st, const Dev &S, const SearchBufs &W, int 
                          int out_stride, int k, int kmul, const int32_t *k_per_query, float *dist,
                          int64_t *labels, const uint64_t *prior, int prior_stride, uint64_t *keys_out) {
     const int np_stride = cls.np_stride;
-    const int npairs = nq * np_stride;
-    const unsigned pb = (unsigned)((npairs + 255) / 256);
-    if (kcap > 64)
-        hipLaunchKernelGGL(k_chunk_merge<true>, dim3(pb), dim3(256), 0, st, S, npairs, W.probes, W.pair_rank,
-                           W.partials, kcap);
-    else
-        hipLaunchKernelGGL(k_chunk_merge<false>, dim3(pb), dim3(256), 0, st, S, npairs, W.probes, W.pair_rank,
-                           W.partials, kcap);
-    hipLaunchKernelGGL(k_merge, dim3((nq + 3) / 4), dim3(256), 0, st, S, nq, np_stride, W.probes, W.pair_rank,
-                       W.partials, kcap, out_stride, k, kmul, k_per_query, dist, labels, cls, prior, prior_stride,
-                       keys_out);
+    // the MFMA scans publish each query's best k-th key; the VALU scan does not
+    const uint32_t *gthr = search_tile(S) == 16 ? W.gthr : nullptr;
+    // results per query beyond 64 need two keys per lane; four waves per query while 4 nq waves fit the chip
+#define SIVF_MERGE(W_, Q_)                                                                                   \
+    hipLaunchKernelGGL((k_merge<W_, Q_>), dim3((nq * Q_ + 3) / 4), dim3(256), 0, st, S, nq, np_stride, W.probes,  \
+                       W.pair_rank, W.partials, kcap, out_stride, k, kmul, k_per_query, dist, labels, cls, gthr,  \
+                       prior, prior_stride, keys_out)
+    const bool wide = kmul * k > 64 && out_stride > 64, few = nq <= FILL_ITEMS / 4;
+    if (wide && few) SIVF_MERGE(true, 4);
+    else if (wide) SIVF_MERGE(true, 1);
+    else if (few) SIVF_MERGE(false, 4);
+    else SIVF_MERGE(false, 1);
+#undef SIVF_MERGE
 }
 
 }  // namespace sivf

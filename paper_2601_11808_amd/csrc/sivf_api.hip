@@ -27,6 +27,8 @@ constexpr int64_t COARSE_BYTES = 256ll << 20;   // scratch for approximate coars
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
+constexpr int64_t FILL_ROOM = 8192;   // chunks beyond one per (query, probe) pair
+
 constexpr int NLISTS = 17;   // per-list scratch arrays
 
 int kcap_for(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : (k <= 64 ? 64 : 128)); }
@@ -75,8 +77,9 @@ Layout make_layout(const sivf_config *c) {
     const int64_t rows_need = c->max_batch > c->max_queries ? c->max_batch : c->max_queries;
     L.coarse_rows = (int)(rows_need < rows_cap ? rows_need : rows_cap);
     const int64_t npairs = (int64_t)c->max_queries * c->max_nprobe;
-    L.max_items = npairs + nl;
-    L.slot_cap = npairs + npairs / 2;   // partial results: one per (pair, list chunk)
+    // a search of few queries splits its lists to fill the chip: room for FILL_ROOM more chunks
+    L.max_items = npairs + nl + FILL_ROOM;
+    L.slot_cap = npairs + (npairs / 2 > FILL_ROOM ? npairs / 2 : FILL_ROOM);   // one per (pair, list chunk)
     size_t cur = 0;
     auto take = [&](size_t bytes) {
         size_t o = cur;
@@ -166,7 +169,7 @@ struct sivf_index {
     ProfClass pc[SIVF_PROF_KINDS];
     // schedule of the k > 64 pass of a certified-scan search (tile, chunk shift, persistent): by
     // default the certified scan with 128-key lists
-    int deep_tile = 16, deep_shift = 14, deep_pers = 1;
+    int deep_tile = 16, deep_shift = 14, deep_pers = 1, deep_auto = 1;
     // host tier (slabs == 0: none): V views the cold pool; its rows and ids sit in
     // caller-provided pinned host memory, the rest in a caller-provided device buffer
     struct {
@@ -337,11 +340,18 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     // (its lists of 128 keys cost the certified scan more than the VALU scan
     // pays); the k <= 64 queries keep the certified scan with 64-key lists.
     const int kw = kcap_for(k);
-    const bool split = ix->S.tile == 16 && kw > 64;
-    Dev Sd = ix->S;
+    // without a schedule of the caller's own, the tiles follow the batch
+    Dev Sm = ix->S, Sd = ix->S;
     Sd.tile = ix->deep_tile;
     Sd.chunk_shift = ix->deep_shift;
     Sd.persistent = ix->deep_pers;
+    Sd.auto_tile = ix->deep_auto;
+    if (Sm.auto_tile) Sm.tile = auto_tile(Sm, nq * stride, false);
+    const bool split = Sm.tile == 16 && kw > 64;
+    if (split && Sd.auto_tile) {
+        Sd.tile = auto_tile(Sd, nq * stride, true);
+        if (Sd.tile != 16) Sd.persistent = 0;
+    }
     struct Pass {
         const Dev *S;
         KClass cls;
@@ -349,9 +359,9 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     } passes[2];
     int np = 0;
     if (!split) {
-        passes[np++] = {&ix->S, kclass_all(stride), kw};
+        passes[np++] = {&Sm, kclass_all(stride), kw};
     } else {
-        if (kpq) passes[np++] = {&ix->S, KClass{kpq, k, stride, -1, 64}, 64};
+        if (kpq) passes[np++] = {&Sm, KClass{kpq, k, stride, -1, 64}, 64};
         passes[np++] = {&Sd, kpq ? KClass{kpq, k, stride, 64, 0x7FFFFFFF} : kclass_all(stride), 128};
     }
     // host tier first: the probed lists' cold segments, scanned in host memory
@@ -423,6 +433,7 @@ sivf_status sivf_create(const sivf_config *cfg, const float *centroids, void *wo
     S.tile = default_tile(cfg->storage, cfg->dim, cfg->slab_capacity, L.kcap);
     S.chunk_shift = DEFAULT_CHUNK_SHIFT;
     S.persistent = 0;
+    S.auto_tile = 1;
     S.hdata = cfg->storage != SIVF_F32 ? (uint4 *)(w + L.hdata) : nullptr;
     S.xnorm = (cfg->storage == SIVF_F32 || cfg->metric == SIVF_L2) ? (float *)(w + L.xnorm) : nullptr;
     ix->W.rr_dist = cfg->storage != SIVF_F32 ? (float *)(w + L.rr_dist) : nullptr;
@@ -576,6 +587,7 @@ sivf_status sivf_tune_search(sivf_index *ix, int64_t nq, const float *q, int32_t
     };
     int bt = ix->S.tile, bs = ix->S.chunk_shift, bp = ix->S.persistent;
     float best = -1.f;
+    ix->S.auto_tile = 0;
     for (int pm = 0; pm < 2 && s == SIVF_OK; pm++)
         for (int T : tiles)
             for (int sh = 10; sh <= 17 && s == SIVF_OK; sh++) {
@@ -597,6 +609,7 @@ sivf_status sivf_tune_search(sivf_index *ix, int64_t nq, const float *q, int32_t
     if (s == SIVF_OK && ix->cfg.storage == SIVF_F32 && bt == 16 && kcap_for(k) > 64) {
         int dt = ix->deep_tile, ds = ix->deep_shift, dp = ix->deep_pers;
         float dbest = -1.f;
+        ix->deep_auto = 0;
         for (int pm = 0; pm < 2 && s == SIVF_OK; pm++)
             for (int T : tiles)
                 for (int sh = 10; sh <= 17 && s == SIVF_OK; sh++) {
@@ -631,6 +644,7 @@ sivf_status sivf_set_search_schedule(sivf_index *ix, int32_t tile, int32_t chunk
     ix->S.tile = tile;
     ix->S.chunk_shift = chunk_shift;
     ix->S.persistent = persistent;
+    ix->S.auto_tile = 0;
     return SIVF_OK;
 }
 
@@ -641,6 +655,7 @@ sivf_status sivf_set_deep_schedule(sivf_index *ix, int32_t tile, int32_t chunk_s
     ix->deep_tile = tile;
     ix->deep_shift = chunk_shift;
     ix->deep_pers = persistent;
+    ix->deep_auto = 0;
     return SIVF_OK;
 }
 

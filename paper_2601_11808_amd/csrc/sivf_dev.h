@@ -51,6 +51,7 @@ struct Dev {
     int dp8;              // ceil(d / 8): 16-byte chunks of a reduced-precision row
     int tile;             // search schedule: queries per work item (fp32 scan: 4 or 8; MFMA scan: 16)
     int chunk_shift;      // search schedule: a work item covers at most 2^chunk_shift list positions
+    int auto_tile;        // 1: no schedule was set or tuned, the tile follows the batch
     int persistent;       // search schedule: 0 = one wave per work item; 1 = resident waves pull items
     int64_t num_slabs, num_pages, dir_cap, id_capacity;
     const float *cent;    // [nlist][dp4*4], zero padded

@@ -91,6 +91,9 @@ int search_tile(const Dev &S);
 // Default queries per work item: 16 (reduced precision, or the certified
 // matrix-core scan where it applies), else 8 (4 past 1024 dimensions).
 int default_tile(int storage, int d, int C, int kcap);
+// Queries per work item of an fp32 search of npairs (query, probe) pairs when no
+// schedule was set; deep: the pass of the queries with k > 64.
+int auto_tile(const Dev &S, int64_t npairs, bool deep);
 // Whether the certified FP32 MFMA scan (tile 16 on fp32 slabs) applies.
 bool cert_ok(int storage, int d, int C, int kcap);
 // Default search chunk: 2^14 positions per work item (a list is split only

@@ -1,0 +1,69 @@
+"""Searches of few queries, on the default (batch-dependent) schedule: tiles of 2
+and 4 queries, lists split into short chunks so that few (query, list) pairs
+fill the chip, and the merge by one or four waves per query.  Results equal the
+oracle's, and those of a schedule set by hand, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2601_11808_amd as sivf
+from tests.gpu_common import compare_results
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(seed, d, sizes, metric, C, max_queries, max_k, max_nprobe):
+    rng = np.random.default_rng(seed)
+    nlist = len(sizes)
+    cent = (rng.standard_normal((nlist, d)) * 6).astype(np.float32)
+    lab = np.repeat(np.arange(nlist), sizes)
+    x = (cent[lab] + rng.standard_normal((lab.shape[0], d))).astype(np.float32)
+    x[1::97] = x[0::97][:x[1::97].shape[0]]          # equal rows under other ids
+    ids = np.arange(x.shape[0])
+    rng.shuffle(x)
+    slabs = x.shape[0] // C + 2 * nlist + 8
+    ix = sivf.Index(d, nlist, cent, metric=metric, slab_capacity=C, num_slabs=slabs, id_capacity=x.shape[0],
+                    max_batch=x.shape[0], max_queries=max_queries, max_k=max_k, max_nprobe=max_nprobe)
+    ref = oracle.OracleIndex(d, nlist, cent, metric, C, slabs, x.shape[0])
+    ix.add(x, ids)
+    assert ix.sync() == 0 and ref.add(x, ids) == 0
+    q = (cent[rng.integers(0, nlist, max_queries)] + rng.standard_normal((max_queries, d))).astype(np.float32)
+    q[0] = x[5]
+    return ix, ref, q
+
+
+# d: float4 rows read through the scalar cache, and rows staged in LDS (d % 4 != 0)
+@pytest.mark.parametrize("metric,d,C", [(0, 32, 64), (1, 30, 32), (0, 300, 128)])
+def test_few_queries_split_lists(metric, d, C):
+    sizes = [30000, 9000, 2000, 700, 129, 128, 64, 1, 0] + [37] * 71
+    ix, ref, q = _index([21, metric, d], d, sizes, metric, C, 1000, 128, 80)
+    default = ix.search_schedule()[0]
+    for nq, k, nprobe in [(1, 1, 1), (1, 10, 80), (1, 128, 80), (2, 65, 9), (5, 64, 3), (70, 16, 7), (768, 10, 2),
+                          (769, 100, 1)]:
+        gd, gl = ix.search(q[:nq], k, nprobe)
+        assert ix.sync() == 0
+        st, rd, rl = ref.search(q[:nq], k, nprobe)
+        assert st == 0
+        assert compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0, (nq, k, nprobe)
+    assert ix.search_schedule()[0] == default        # the rule changes no setting
+    # the same batch under every schedule the caller can set
+    kpq = np.random.default_rng(3).choice(np.array([0, 1, 10, 100, 128], np.int32), 40)
+    npq = np.random.default_rng(4).integers(1, 81, 40).astype(np.int32)
+    want = [t.cpu().numpy() for t in ix.search(q[:40], 128, 1, k_per_query=kpq, nprobe_per_query=npq)]
+    st, rd, rl = ref.search(q[:40], 128, 1, k_per_query=kpq, nprobe_per_query=npq)
+    assert st == 0 and compare_results(*want, rd, rl) == 0
+    for sched in [(4, 6, 0), (4, 14, 1), (8, 9, 0)] + ([(16, 6, 0), (16, 13, 1)] if d <= 256 else []):
+        ix.set_search_schedule(*sched)
+        got = [t.cpu().numpy() for t in ix.search(q[:40], 128, 1, k_per_query=kpq, nprobe_per_query=npq)]
+        assert all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(want, got)), sched
+
+
+def test_few_queries_small_buffers():
+    """An index planned for one query of eight probes: the split stays within its buffers."""
+    sizes = [20000, 5000, 300] + [5] * 13
+    ix, ref, q = _index([22], 16, sizes, 0, 64, 1, 128, 8)
+    for k in (1, 128):
+        gd, gl = ix.search(q[:1], k, 8)
+        assert ix.sync() == 0
+        st, rd, rl = ref.search(q[:1], k, 8)
+        assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
