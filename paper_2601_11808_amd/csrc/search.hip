@@ -14,8 +14,9 @@
 //
 //   k_inv_count   rank of each (query, probe) pair within its list (or
 //                 k_inv_count_lds: block histograms, fewer global atomics)
-//   k_inv_plan    per-list pair offsets; work items (list, tile)
-//   k_inv_scatter pair ids grouped by list
+//   k_inv_plan    per-list pair offsets, chunks, item offsets
+//   k_inv_fill    work items (list, tile, chunk); pair ids grouped by list
+//   (k_inv_small  the three in one launch, for small batches)
 //   k_scan        one wave per item: distances + per-query top-kcap
 //   k_merge       one wave per query: kcap-way merge of its probe partials
 #include "sivf_launch.h"
@@ -39,8 +40,10 @@ __device__ __forceinline__ int pair_list(const int32_t *probes, int p, const KCl
 }
 
 __global__ __launch_bounds__(256) void k_inv_count(Dev S, int npairs, const int32_t *__restrict__ probes,
-                                                   int32_t *__restrict__ pair_rank, KClass cls) {
+                                                   int32_t *__restrict__ pair_rank, KClass cls, int nq,
+                                                   uint32_t *__restrict__ gthr) {
     const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p < nq) gthr[p] = 0xFFFFFFFFu;   // no key published yet
     const bool active = p < npairs;
     const int l = active ? pair_list(probes, p, cls) : -1;
     const bool act = l >= 0;
@@ -55,9 +58,11 @@ __global__ __launch_bounds__(256) void k_inv_count(Dev S, int npairs, const int3
 // and adds that base.  Used when the histogram fits in 64 KiB.
 constexpr int INV_PB = 8192;
 __global__ __launch_bounds__(1024) void k_inv_count_lds(Dev S, int npairs, const int32_t *__restrict__ probes,
-                                                        int32_t *__restrict__ pair_rank, KClass cls) {
+                                                        int32_t *__restrict__ pair_rank, KClass cls, int nq,
+                                                        uint32_t *__restrict__ gthr) {
     extern __shared__ int32_t hist[];
     const int tid = threadIdx.x;
+    for (int i = blockIdx.x * 1024 + tid; i < nq; i += gridDim.x * 1024) gthr[i] = 0xFFFFFFFFu;   // none published yet
     const int64_t p0 = (int64_t)blockIdx.x * INV_PB;
     const int n = (int)min((int64_t)INV_PB, (int64_t)npairs - p0);
     for (int i = tid; i < S.nlist; i += 1024) hist[i] = 0;
@@ -125,104 +130,128 @@ __device__ __forceinline__ int plan_shift(long long cost, int sh0, int T) {
     return min(s, sh0);
 }
 
-// One block plans the whole search:
+// One block of 1,024 threads plans the whole search:
 //  1. snapshot every list's length (the scan reads only these entries; a
 //     second pass of the same search keeps the first pass's snapshot) and
 //     lay out the (query, probe) pairs list by list;
-//  2. split lists into chunks of 2^sh positions, with the smallest sh >= sh0
-//     whose partial results (one per pair and chunk) and work items (one per
-//     tile of T pairs and chunk) fit their buffers -- a long list is scanned
-//     by many waves at once instead of one;
+//  2. split lists into chunks of 2^sh positions (plan_shift), with the smallest
+//     sh from there up whose partial results (one per pair and chunk) and work
+//     items (one per tile of T pairs and chunk) fit their buffers;
 //  3. per-list offsets of partial slots and items; reset the work counters;
 //  4. cut the items into 8 ranges, one per XCD, of equal scan cost (list
 //     positions x query tiles) -- equal item counts leave XCDs idle while
 //     others finish long lists -- each at most xcd_cap items (the blocks an
 //     XCD receives in the dispatch schedule).
-__global__ __launch_bounds__(1024) void k_inv_plan(Dev S, int T, int sh0, int64_t slot_cap, int64_t item_cap,
-                                                   int xcd_cap, int snap, int32_t *__restrict__ heat) {
-    __shared__ int sbuf[16];
-    __shared__ long long sred[32];
-    __shared__ long long scost[16];
-    __shared__ int sxb[9];
-    int carry_p = 0;
-    for (int base = 0; base < S.nlist; base += 1024) {
-        const int l = base + threadIdx.x;
-        const bool valid = l < S.nlist;
-        const int qc = valid ? S.l_qc[l] : 0;
-        int tp;
-        const int ep = block_excl_scan<1024>(qc, sbuf, &tp);
-        if (valid) {
-            if (snap) S.l_snap[l] = S.len[l];
-            // probe count per list (host tier: the coldest lists are offloaded first), saturating
-            if (heat && qc > 0) heat[l] = (int32_t)min((int64_t)heat[l] + qc, (int64_t)0x7FFFFFFF);
-            S.l_qoff[l] = carry_p + ep;
-            S.l_qcs[l] = qc;
-            S.l_qc[l] = 0;
+// Wave w holds lists 64 E w + 64 e + lane, e < E, in registers, so every array is
+// read once, coalesced, and the four prefix sums take one DPP scan per 64 lists
+// and one exchange between the waves.  What bounds it is latency on one CU: at
+// 16,384 lists a loop of block-wide scans over 1,024 lists at a time took 101 us.
+struct PlanShared {
+    int wt[4][16];
+    long long red[32];
+    int xb[9];
+};
+
+// Totals of four values over the block's waves, and each wave's exclusive sums.
+__device__ __forceinline__ void wave_offsets4(int (&v)[4], int (&before)[4], int (&total)[4], PlanShared &sm) {
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        int x = v[i];
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane_id() == 0) sm.wt[i][w] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        before[i] = total[i] = 0;
+        for (int j = 0; j < 16; j++) {
+            const int x = sm.wt[i][j];
+            before[i] += j < w ? x : 0;
+            total[i] += x;
         }
-        carry_p += tp;
     }
-    // each thread re-reads only the lists it wrote above
-    // total scan cost (list positions x query tiles)
-    long long wsum = 0, wdummy = 0;
-    for (int l = threadIdx.x; l < S.nlist; l += 1024) {
-        const int qc = S.l_qcs[l];
-        if (qc > 0) wsum += (long long)cdiv_s(qc, T) * S.l_snap[l];
-    }
-    block_sum2(wsum, wdummy, sred);
-    int sh = plan_shift(wsum, sh0, T);
+}
+
+// qc, len: pairs and snapshot length of this thread's lists.  qoff_l, ioff_l (or
+// NULL): copies of the pair and item offsets in LDS.  Returns the item count.
+template <int E>
+__device__ __forceinline__ int plan_core(const Dev &S, int T, int sh0, int64_t slot_cap, int64_t item_cap,
+                                         int xcd_cap, const int (&qc)[E], const int (&len)[E], int *qoff_l,
+                                         int *ioff_l, PlanShared &sm) {
+    const int lane = lane_id(), l0 = (threadIdx.x >> 6) * 64 * E + lane;
+    long long cost = 0, none = 0;
+#pragma unroll
+    for (int e = 0; e < E; e++) cost += qc[e] > 0 ? (long long)cdiv_s(qc[e], T) * len[e] : 0;
+    block_sum2(cost, none, sm.red);
+    int sh = plan_shift(cost, sh0, T);
     for (;;) {
         long long slots = 0, items = 0;
-        for (int l = threadIdx.x; l < S.nlist; l += 1024) {
-            const int qc = S.l_qcs[l];
-            const int nc = qc > 0 ? list_chunks(S.l_snap[l], sh) : 0;
-            slots += (long long)qc * nc;
-            items += (long long)cdiv_s(qc, T) * nc;
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            const int nc = qc[e] > 0 ? list_chunks(len[e], sh) : 0;
+            slots += (long long)qc[e] * nc;
+            items += (long long)cdiv_s(qc[e], T) * nc;
         }
-        block_sum2(slots, items, sred);
+        block_sum2(slots, items, sm.red);
         if ((slots <= slot_cap && items <= item_cap) || sh >= 31) break;   // sh = 31: one chunk per list
         sh++;
     }
-    // the total cost is known, so each list can tell which XCD boundaries fall in it
-    if (threadIdx.x < 9) sxb[threadIdx.x] = -1;
-    __syncthreads();
-    int carry_s = 0, carry_i = 0;
-    long long carry_w = 0;
-    for (int base = 0; base < S.nlist; base += 1024) {
-        const int l = base + threadIdx.x;
-        const bool valid = l < S.nlist;
-        const int qc = valid ? S.l_qcs[l] : 0;
-        const int len = valid ? S.l_snap[l] : 0;
-        const int nc = qc > 0 ? list_chunks(len, sh) : 0;
-        const int ni = cdiv_s(qc, T) * nc;
-        const long long wl = nc > 0 ? (long long)cdiv_s(qc, T) * len : 0;
-        int ts, ti;
-        long long tw;
-        const int es = block_excl_scan<1024>(qc * nc, sbuf, &ts);
-        const int ei = block_excl_scan<1024>(ni, sbuf, &ti);
-        const long long ew = block_excl_scan64<1024>(wl, scost, &tw);
-        if (valid) {
-            S.l_pbase[l] = carry_s + es;
-            S.l_ioff[l] = carry_i + ei;
-            // XCD boundary x (1..7) at cost x * W / 8 falls in this list's [w0, w0 + wl)
-            const long long w0 = carry_w + ew;
-            for (int x = 1; x < 8 && wl > 0; x++) {
-                const long long target = wsum * x / 8;
-                if (target >= w0 && target < w0 + wl)
-                    sxb[x] = carry_i + ei + (int)((double)(target - w0) / (double)wl * ni);
+    // costs in units that keep their sum below 2^30 (the cuts need no more)
+    const int cb = max(0, 34 - (int)__clzll(cost));
+    auto values = [&](int e, int (&v)[4]) {
+        const int nc = qc[e] > 0 ? list_chunks(len[e], sh) : 0, nt = cdiv_s(qc[e], T);
+        v[0] = qc[e];
+        v[1] = qc[e] * nc;
+        v[2] = nt * nc;
+        v[3] = nc > 0 ? (int)(((long long)nt * len[e]) >> cb) : 0;
+    };
+    int sum[4] = {0, 0, 0, 0}, carry[4], total[4];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        int v[4];
+        values(e, v);
+#pragma unroll
+        for (int i = 0; i < 4; i++) sum[i] += v[i];
+    }
+    if (threadIdx.x < 9) sm.xb[threadIdx.x] = -1;
+    wave_offsets4(sum, carry, total, sm);
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int l = l0 + 64 * e;
+        int v[4], ex[4];
+        values(e, v);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int incl = wave_incl_scan_dpp(v[i]);
+            ex[i] = carry[i] + incl - v[i];
+            carry[i] += readlane_i(incl, 63);
+        }
+        if (l < S.nlist) {
+            S.l_qoff[l] = ex[0];
+            S.l_pbase[l] = ex[1];
+            S.l_ioff[l] = ex[2];
+            S.l_qcs[l] = qc[e];
+            if (qoff_l) {
+                qoff_l[l] = ex[0];
+                ioff_l[l] = ex[2];
+            }
+            // XCD boundary x (1..7) at cost x * W / 8 falls in this list's [ex, ex + v)
+            for (int x = 1; x < 8 && v[3] > 0; x++) {
+                const int target = (int)((long long)total[3] * x / 8);
+                if (target >= ex[3] && target < ex[3] + v[3])
+                    sm.xb[x] = ex[2] + (int)((double)(target - ex[3]) / (double)v[3] * v[2]);
             }
         }
-        carry_s += ts;
-        carry_i += ti;
-        carry_w += tw;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int n = carry_i;
+        const int n = total[2];
         // boundaries not hit (zero-cost tail) follow the previous one; then cap every range
         int b = 0;
         S.ctl[CTL_XB] = 0;
         for (int x = 1; x < 8; x++) {
-            int t = sxb[x] < 0 ? b : sxb[x];
+            int t = sm.xb[x] < 0 ? b : sm.xb[x];
             t = t < b ? b : t;
             t = t > b + xcd_cap ? b + xcd_cap : t;               // this range fits its XCD's blocks
             const int rest = n - (8 - x) * xcd_cap;               // the later ranges must fit too
@@ -236,12 +265,54 @@ __global__ __launch_bounds__(1024) void k_inv_plan(Dev S, int T, int sh0, int64_
         S.ctl[CTL_CHUNK] = sh;
     }
     if (threadIdx.x < 8) S.ctl[CTL_WORK0 + CTL_WORK_STRIDE * threadIdx.x] = 0;
+    return total[2];
 }
 
-// Work items of each list, chunk-major (consecutive items read the same
-// slabs for different query tiles).  One wave per list.
-__global__ __launch_bounds__(256) void k_inv_items(Dev S, int T, int32_t *__restrict__ item_list,
-                                                   int32_t *__restrict__ item_tile, int32_t *__restrict__ item_chunk) {
+// Length of list l as this pass scans it, and the probe count per list (host
+// tier: the coldest lists are offloaded first), saturating.
+__device__ __forceinline__ int plan_len(const Dev &S, int l, int qc, int snap, int32_t *heat) {
+    int len;
+    if (snap) {
+        len = S.len[l];
+        S.l_snap[l] = len;
+    } else {
+        len = S.l_snap[l];
+    }
+    if (heat && qc > 0) heat[l] = (int32_t)min((int64_t)heat[l] + qc, (int64_t)0x7FFFFFFF);
+    return len;
+}
+
+template <int E>
+__global__ __launch_bounds__(1024) void k_inv_plan(Dev S, int T, int sh0, int64_t slot_cap, int64_t item_cap,
+                                                   int xcd_cap, int snap, int32_t *__restrict__ heat) {
+    __shared__ PlanShared sm;
+    const int l0 = (threadIdx.x >> 6) * 64 * E + lane_id();
+    int qc[E], len[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int l = l0 + 64 * e;
+        qc[e] = l < S.nlist ? S.l_qc[l] : 0;
+        len[e] = l < S.nlist ? plan_len(S, l, qc[e], snap, heat) : 0;
+        if (l < S.nlist) S.l_qc[l] = 0;
+    }
+    plan_core<E>(S, T, sh0, slot_cap, item_cap, xcd_cap, qc, len, nullptr, nullptr, sm);
+}
+
+// The rest of the plan, on as many blocks as it takes: the first item_blocks
+// blocks list each list's work items, chunk-major (consecutive items read the
+// same slabs for different query tiles), one wave per list; the others group the
+// pairs by list.
+__global__ __launch_bounds__(256) void k_inv_fill(Dev S, int T, int item_blocks, int npairs,
+                                                  const int32_t *__restrict__ probes,
+                                                  const int32_t *__restrict__ pair_rank,
+                                                  int32_t *__restrict__ list_pairs, int32_t *__restrict__ item_list,
+                                                  int32_t *__restrict__ item_tile, int32_t *__restrict__ item_chunk) {
+    if ((int)blockIdx.x >= item_blocks) {
+        const int p = ((int)blockIdx.x - item_blocks) * 256 + threadIdx.x;
+        const int r = p < npairs ? pair_rank[p] : -1;
+        if (r >= 0) list_pairs[S.l_qoff[probes[p]] + r] = p;
+        return;
+    }
     const int l = blockIdx.x * 4 + (threadIdx.x >> 6), lane = lane_id();
     if (l >= S.nlist) return;
     const int qc = S.l_qcs[l];
@@ -256,14 +327,63 @@ __global__ __launch_bounds__(256) void k_inv_items(Dev S, int T, int32_t *__rest
     }
 }
 
-__global__ __launch_bounds__(256) void k_inv_scatter(Dev S, int npairs, const int32_t *__restrict__ probes,
-                                                     const int32_t *__restrict__ pair_rank,
-                                                     int32_t *__restrict__ list_pairs) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= npairs) return;
-    const int r = pair_rank[p];
-    if (r < 0) return;
-    list_pairs[S.l_qoff[probes[p]] + r] = p;
+// The whole plan in one launch, for at most SP_PAIRS pairs on at most SP_LISTS
+// lists: ranks from an LDS histogram, then plan_core, then pairs and items from
+// the offsets in LDS (an item finds its list by bisection).  A launch that finds
+// the previous one's results costs about 4.5 us here, more than the work of any of
+// the five kernels it replaces (count, plan, items, pairs, threshold fill).
+constexpr int SP_PAIRS = 8192, SP_LISTS = 4096, SP_E = SP_LISTS / 1024;
+__global__ __launch_bounds__(1024) void k_inv_small(Dev S, int T, int sh0, int64_t slot_cap, int64_t item_cap,
+                                                    int xcd_cap, int snap, int32_t *__restrict__ heat, int nq,
+                                                    int npairs, const int32_t *__restrict__ probes,
+                                                    int32_t *__restrict__ pair_rank, int32_t *__restrict__ list_pairs,
+                                                    int32_t *__restrict__ item_list, int32_t *__restrict__ item_tile,
+                                                    int32_t *__restrict__ item_chunk, KClass cls,
+                                                    uint32_t *__restrict__ gthr) {
+    extern __shared__ int32_t lds[];   // pairs per list, then pair offsets, then item offsets (nlist each)
+    __shared__ PlanShared sm;
+    int32_t *hist = lds, *qoff = lds + S.nlist, *ioff = lds + 2 * S.nlist;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < nq; i += 1024) gthr[i] = 0xFFFFFFFFu;   // no key published yet
+    for (int i = tid; i < S.nlist; i += 1024) hist[i] = 0;
+    int pl[SP_PAIRS / 1024], pr[SP_PAIRS / 1024];
+#pragma unroll
+    for (int i = 0; i < SP_PAIRS / 1024; i++) {
+        const int p = tid + 1024 * i;
+        pl[i] = p < npairs ? pair_list(probes, p, cls) : -1;
+    }
+    const int l0 = (tid >> 6) * 64 * SP_E + lane_id();
+    int qc[SP_E], len[SP_E];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SP_PAIRS / 1024; i++) pr[i] = pl[i] >= 0 ? atomicAdd(&hist[pl[i]], 1) : -1;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < SP_E; e++) {
+        const int l = l0 + 64 * e;
+        qc[e] = l < S.nlist ? hist[l] : 0;
+        len[e] = l < S.nlist ? plan_len(S, l, qc[e], snap, heat) : 0;
+    }
+    const int n = plan_core<SP_E>(S, T, sh0, slot_cap, item_cap, xcd_cap, qc, len, qoff, ioff, sm);
+    // plan_core's last barrier is behind its LDS writes
+#pragma unroll
+    for (int i = 0; i < SP_PAIRS / 1024; i++) {
+        const int p = tid + 1024 * i;
+        if (p < npairs) pair_rank[p] = pr[i];
+        if (pr[i] >= 0) list_pairs[qoff[pl[i]] + pr[i]] = p;
+    }
+    for (int i = tid; i < n; i += 1024) {
+        int lo = 0, hi = S.nlist - 1;   // the last list whose first item is at most i holds it
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (ioff[mid] <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        const int nt = cdiv_s(hist[lo], T), j = i - ioff[lo];
+        item_list[i] = lo;
+        item_chunk[i] = j / nt;
+        item_tile[i] = j % nt;
+    }
 }
 
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
@@ -1577,7 +1697,6 @@ void launch_search_scan_mfma(hipStream_t st, const Dev &S, const SearchBufs &W, 
     const int npairs = nq * np_stride;
     // k-blocks of 32 dimensions held as B operands: 2, 3, 4 or 8 (d <= 256)
     const int nkb = (S.d + 31) / 32;
-    launch_fill_i32(st, reinterpret_cast<int32_t *>(W.gthr), nq, -1);   // no key published yet
 #define SIVF_LAUNCH_MFMA_P(M, D, K, P)                                                                       \
     hipLaunchKernelGGL((k_scan_mfma<M, D, K, P>), dim3(scan_grid(k_scan_mfma<M, D, K, P>, S, W, npairs, 0)),    \
                        dim3(64), 0, st, S, W.item_list, W.item_tile, W.item_chunk, W.list_pairs, q, np_stride,  \
@@ -1638,20 +1757,32 @@ void launch_search_plan(hipStream_t st, const Dev &S, const SearchBufs &W, int n
                         int32_t *heat) {
     const int np_stride = cls.np_stride;
     const int npairs = nq * np_stride;
-    const unsigned pb = (unsigned)((npairs + 255) / 256);
     const int T = search_tile(S);
+    const int64_t lim = item_limit(S, W, npairs);
+    const int xcd_cap = (int)((lim + 7) / 8);
+    if (npairs <= SP_PAIRS && S.nlist <= SP_LISTS) {
+        hipLaunchKernelGGL(k_inv_small, dim3(1), dim3(1024), (size_t)S.nlist * 12, st, S, T, S.chunk_shift, W.slot_cap,
+                           lim, xcd_cap, snap, heat, nq, npairs, W.probes, W.pair_rank, W.list_pairs, W.item_list,
+                           W.item_tile, W.item_chunk, cls, W.gthr);
+        return;
+    }
+    const unsigned pb = (unsigned)((npairs + 255) / 256);
     if (S.nlist <= 16384)
         hipLaunchKernelGGL(k_inv_count_lds, dim3((unsigned)((npairs + INV_PB - 1) / INV_PB)), dim3(1024),
-                           (size_t)S.nlist * 4, st, S, npairs, W.probes, W.pair_rank, cls);
+                           (size_t)S.nlist * 4, st, S, npairs, W.probes, W.pair_rank, cls, nq, W.gthr);
     else
-        hipLaunchKernelGGL(k_inv_count, dim3(pb), dim3(256), 0, st, S, npairs, W.probes, W.pair_rank, cls);
-    const int64_t lim = item_limit(S, W, npairs);
-    hipLaunchKernelGGL(k_inv_plan, dim3(1), dim3(1024), 0, st, S, T, S.chunk_shift, W.slot_cap, lim,
-                       (int)((lim + 7) / 8), snap, heat);
-    hipLaunchKernelGGL(k_inv_items, dim3((S.nlist + 3) / 4), dim3(256), 0, st, S, T, W.item_list, W.item_tile,
-                       W.item_chunk);
-    hipLaunchKernelGGL(k_inv_scatter, dim3(pb), dim3(256), 0, st, S, npairs, W.probes, W.pair_rank,
-                       W.list_pairs);
+        hipLaunchKernelGGL(k_inv_count, dim3(pb), dim3(256), 0, st, S, npairs, W.probes, W.pair_rank, cls, nq, W.gthr);
+#define SIVF_PLAN(E)                                                                                          \
+    hipLaunchKernelGGL(k_inv_plan<E>, dim3(1), dim3(1024), 0, st, S, T, S.chunk_shift, W.slot_cap, lim, xcd_cap, \
+                       snap, heat)
+    if (S.nlist <= 1024) SIVF_PLAN(1);
+    else if (S.nlist <= 4096) SIVF_PLAN(4);
+    else if (S.nlist <= 16384) SIVF_PLAN(16);
+    else SIVF_PLAN(64);
+#undef SIVF_PLAN
+    const unsigned ib = (unsigned)((S.nlist + 3) / 4);
+    hipLaunchKernelGGL(k_inv_fill, dim3(ib + pb), dim3(256), 0, st, S, T, (int)ib, npairs, W.probes, W.pair_rank,
+                       W.list_pairs, W.item_list, W.item_tile, W.item_chunk);
 }
 
 bool cert_ok(int storage, int d, int C, int kcap) { return storage == 0 && d <= 256 && C >= 4 && kcap <= 128; }
@@ -1676,7 +1807,6 @@ static void launch_cert(hipStream_t st, const Dev &S, const SearchBufs &W, const
     // sorted lists of 16 keys (kcap 16: four queries per register), 64 (kcap 32, 64) or
     // 128 (kcap 128: ranks 64..127 in the partial slot)
     const int nb = (S.d + 15) / 16;
-    launch_fill_i32(st, reinterpret_cast<int32_t *>(W.gthr), npairs / np_stride, -1);   // no key published yet
 #define SIVF_CERT_NB(KC)                                                                                     \
     do {                                                                                                     \
         if (nb <= 2) launch_cert_nb<METRIC, 2, KC>(st, S, W, q, np_stride, kcap, k, kpq, npairs);            \
