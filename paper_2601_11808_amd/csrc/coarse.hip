@@ -269,6 +269,93 @@ __global__ __launch_bounds__(256) void k_coarse_gemm(const float *__restrict__ X
     }
 }
 
+// The same approximate distances for batches too small to fill the chip with
+// 128 x 128 tiles (1 query x 1,024 lists were 8 blocks and 19 us): one wave per 16
+// rows x 16 LT lists, both operands read from global memory in the MFMA layout
+// (lane l: row or list l % 16, the 4 dimensions of chunk 4 b + l / 16), U chunks of
+// each in flight, nothing staged and no barrier.  What bounds it is the latency of
+// ceil(d / (16 U)) rounds of loads; each wave reads its centroids once per 16 rows, so
+// the tiled kernel takes over where its blocks cover the chip.
+template <int METRIC, bool VEC, int LT>
+__global__ __launch_bounds__(256) void k_coarse_small(const float *__restrict__ X, int n, int d,
+                                                      const float *__restrict__ cent, int dpad,
+                                                      const float *__restrict__ cn2, int nlist,
+                                                      float *__restrict__ out, const int32_t *ctl, int gated) {
+    constexpr int U = 4;
+    if (gated && call_failed(ctl)) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, kg = lane >> 4;
+    const int nlb = (nlist + 64 * LT - 1) / (64 * LT);   // blocks of 4 waves x 16 LT lists
+    const int r = ((int)blockIdx.x / nlb) * 16 + col;
+    const int l0 = ((int)blockIdx.x % nlb) * 64 * LT + w * 16 * LT;
+    if (l0 >= nlist) return;
+    const int nch = dpad >> 2;
+    const float *xr = X + (int64_t)(r < n ? r : 0) * d;
+    const float *cr[LT];
+#pragma unroll
+    for (int t = 0; t < LT; t++) cr[t] = cent + (int64_t)min(l0 + 16 * t + col, nlist - 1) * dpad;
+    floatx4 acc[LT];
+#pragma unroll
+    for (int t = 0; t < LT; t++) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float sq = 0.f;
+    for (int b0 = 0; b0 < nch; b0 += 4 * U) {
+        float4 xv[U], cv[U][LT];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int c = b0 + 4 * u + kg;
+            const bool in = c < nch;   // past the row: the row operand is zero, the list operand any finite value
+            const int cc = in ? c : nch - 1;
+#pragma unroll
+            for (int t = 0; t < LT; t++) cv[u][t] = reinterpret_cast<const float4 *>(cr[t])[cc];
+            if (VEC) {
+                xv[u] = in && r < n ? reinterpret_cast<const float4 *>(xr)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+            } else {
+                const int j = 4 * c;
+                xv[u].x = r < n && j < d ? xr[j] : 0.f;
+                xv[u].y = r < n && j + 1 < d ? xr[j + 1] : 0.f;
+                xv[u].z = r < n && j + 2 < d ? xr[j + 2] : 0.f;
+                xv[u].w = r < n && j + 3 < d ? xr[j + 3] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            sq = fmaf(xv[u].x, xv[u].x, sq);
+            sq = fmaf(xv[u].y, xv[u].y, sq);
+            sq = fmaf(xv[u].z, xv[u].z, sq);
+            sq = fmaf(xv[u].w, xv[u].w, sq);
+#pragma unroll
+            for (int t = 0; t < LT; t++) {
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[u][t].x, xv[u].x, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[u][t].y, xv[u].y, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[u][t].z, xv[u].z, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[u][t].w, xv[u].w, acc[t], 0, 0, 0);
+            }
+        }
+    }
+    sq += __shfl_xor(sq, 16);
+    sq += __shfl_xor(sq, 32);
+    if (r >= n) return;
+    // lane: row col, lists l0 + 16 t + 4 kg .. +3
+    const bool vec4 = (nlist & 3) == 0;
+#pragma unroll
+    for (int t = 0; t < LT; t++) {
+        const int lb = l0 + 16 * t + 4 * kg;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const float c2 = (METRIC == 0 && lb + e < nlist) ? cn2[lb + e] : 0.f;
+            v[e] = METRIC == 0 ? (sq + c2) - 2.0f * acc[t][e] : -acc[t][e];
+        }
+        float *o = out + (int64_t)r * nlist + lb;
+        if (vec4 && lb + 3 < nlist) {
+            *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (lb + e < nlist) o[e] = v[e];
+        }
+    }
+}
+
 // Certified bound on |Dt - D| for a row of norm qn and a list of norm cn: the
 // FP32 arithmetic of the GEMM ((4d+16) 2^-24 (|x|+|c|)^2, IP: |x||c|, plus
 // an underflow term) and, with bf16 operands (bf = 1), their rounding:
@@ -544,24 +631,50 @@ __device__ __forceinline__ double canon_dist(const float *x, const float *__rest
     return metric == 0 ? r : -r;
 }
 
-constexpr int SEL_CAP = 512;   // candidates buffered per exact re-check round
+// A float that is below first - 2 emax: a distance under it is certainly among
+// the m smallest, where `first` is at most the m-th smallest approximate one.
+__device__ __forceinline__ float sure_below(float first, double emax) {
+    const float f = (float)((double)first - 2.0 * emax);
+    return f - (fabsf(f) * 0x1p-22f + 0x1p-120f);
+}
 
-// One block of 256 threads per row.  Dynamic shared memory:
+constexpr int SEL_CAP = 512;   // candidates buffered per exact re-check round
+constexpr int SEL_BINS = 1024;
+
+// One block of 256 threads per row; the row's approximate distances sit in
+// registers (thread t holds lists t + 256 i, i < NK; NK = 0: any number of
+// lists, read again on each pass).
+// The bound: a histogram of the distances over [smallest, largest] finds the
+// bin that holds the m-th smallest; while that bin holds many more than m needs, it
+// is split the same way.  The largest distance tau' up to its end is at least the
+// m-th smallest, and the candidates tau' admits are a superset of those the m-th
+// smallest itself would.  (A radix histogram of the keys' top bits sends every
+// list to one bin, whose LDS atomics serialise: 4,096 lists took 527 us for 16,000
+// rows.)
+// ordered = 0 (a search needs the probe set, not its order): no exact m-th
+// distance is below the smallest distance of that bin by more than max E, so a
+// list below it by more than 2 max E is in the set without an exact distance, and
+// only the lists around the bin are re-checked.  The re-check reads one
+// centroid row per lane (16 bytes of 64 lines per load) and took most of the time.
+// Dynamic shared memory:
 //   sx[dpad] float | kd[mmax] kl[mmax] nd[mmax] nl[mmax] | cd[SEL_CAP] cl[SEL_CAP]
-__global__ __launch_bounds__(256) void k_coarse_select(
+template <int NK>
+__global__ __launch_bounds__(256, NK <= 16 ? 6 : 1) void k_coarse_select(
     const float *__restrict__ dt, const float *__restrict__ X, int n, int d, const float *__restrict__ cent,
     int dpad, const double *__restrict__ cnorm, const double *__restrict__ cmax, int nlist, int metric,
     int m_uniform, const int32_t *__restrict__ m_per_row, int mmax, int32_t *__restrict__ out,
-    int out_stride, const int32_t *ctl, int gated, int bf) {
+    int out_stride, const int32_t *ctl, int gated, int bf, int ordered) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int hist[256];
+    __shared__ __align__(16) int hist[SEL_BINS];
     __shared__ int sbuf[8];
     __shared__ double sred[4];
-    __shared__ int sdig[2];
+    __shared__ float sext[2][4];
+    __shared__ int spick[3];
+    __shared__ int scand, sdef;
     if (gated && call_failed(ctl)) return;
     const int row = blockIdx.x;
     if (row >= n) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     double *kd = (double *)smem;
     double *nd = kd + mmax;
     double *cd = nd + mmax;
@@ -574,6 +687,22 @@ __global__ __launch_bounds__(256) void k_coarse_select(
     m = m < nlist ? m : nlist;
     m = m < mmax ? m : mmax;
     m = m < 1 ? 1 : m;
+    const float *drow = dt + (int64_t)row * nlist;
+    float key[NK ? NK : 1];
+    if (NK) {
+#pragma unroll
+        for (int i = 0; i < NK; i++) key[i] = tid + 256 * i < nlist ? drow[tid + 256 * i] : 0.f;
+    }
+    // f(list, distance) for every list of this thread
+    auto each = [&](auto f) {
+        if constexpr (NK > 0) {
+#pragma unroll
+            for (int i = 0; i < NK; i++)
+                if (tid + 256 * i < nlist) f(tid + 256 * i, key[i]);
+        } else {
+            for (int l = tid; l < nlist; l += 256) f(l, drow[l]);
+        }
+    };
     const float *xr = X + (int64_t)row * d;
     double q2 = 0.0;
     for (int j = tid; j < dpad; j += 256) {
@@ -582,7 +711,8 @@ __global__ __launch_bounds__(256) void k_coarse_select(
         q2 = __fma_rn((double)v, (double)v, q2);
     }
     for (int o = 32; o > 0; o >>= 1) q2 += __shfl_xor(q2, o);
-    if ((tid & 63) == 0) sred[tid >> 6] = q2;
+    if (lane == 0) sred[w] = q2;
+    if (tid == 0) scand = sdef = 0;
     __syncthreads();
     const double qn = sqrt(sred[0] + sred[1] + sred[2] + sred[3]) * (1.0 + 0x1p-50);
     const double cm = *cmax;
@@ -591,34 +721,80 @@ __global__ __launch_bounds__(256) void k_coarse_select(
     // the GEMM can overflow, so every approximation is finite and the bound
     // holds; above it (or for a non-finite norm) every list is re-checked.
     const bool every = !(qn + cm < 0x1p60);
-    const float *drow = dt + (int64_t)row * nlist;
 
-    // tau = m-th smallest approximate distance (radix select on ordered bits).
-    uint32_t prefix = 0, pmask = 0;
-    int rem = m;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0;
-        __syncthreads();
-        for (int l = tid; l < nlist; l += 256) {
-            const uint32_t key = ord_bits(drow[l]);
-            if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1);
+    // smallest and largest of the lists f selects (block-wide; ends with a barrier)
+    auto extent = [&](auto sel, float &lo, float &hi) {
+        lo = __builtin_inff();
+        hi = -__builtin_inff();
+        each([&](int, float v) {
+            if (sel(v)) {
+                lo = fminf(lo, v);
+                hi = fmaxf(hi, v);
+            }
+        });
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o));
+            hi = fmaxf(hi, __shfl_xor(hi, o));
+        }
+        __syncthreads();   // the last readers of sext are done
+        if (lane == 0) {
+            sext[0][w] = lo;
+            sext[1][w] = hi;
         }
         __syncthreads();
-        const int h = hist[tid];
-        int tot;
-        const int ex = block_excl_scan<256>(h, sbuf, &tot);
-        if (ex < rem && rem <= ex + h) {
-            sdig[0] = tid;
-            sdig[1] = ex;
+        lo = fminf(fminf(sext[0][0], sext[0][1]), fminf(sext[0][2], sext[0][3]));
+        hi = fmaxf(fmaxf(sext[1][0], sext[1][1]), fmaxf(sext[1][2], sext[1][3]));
+    };
+    double ub = 0.0;
+    float sure = -__builtin_inff();   // lists below it are in the set
+    if (!every) {
+        float lo, hi;
+        extent([](float) { return true; }, lo, hi);
+        int below = 0;   // lists under lo, all among the candidates
+        float tau = hi, first = lo;
+        for (int round = 0; round < 3 && lo < hi; round++) {
+            // bin of a distance in [lo, hi]: monotone in it (each operation rounds monotonically)
+            const float range = hi - lo, scale = range > 0x1p-100f ? (SEL_BINS - 1) / range : 0.f;
+            auto bin = [&](float v) { return min((int)((v - lo) * scale), SEL_BINS - 1); };
+            for (int i = tid; i < SEL_BINS; i += 256) hist[i] = 0;
+            __syncthreads();
+            each([&](int, float v) {
+                if (v >= lo && v <= hi) atomicAdd(&hist[bin(v)], 1);
+            });
+            __syncthreads();
+            const int4 h = *reinterpret_cast<const int4 *>(&hist[4 * tid]);
+            const int hs[4] = {h.x, h.y, h.z, h.w};
+            int tot;
+            int ex = below + block_excl_scan<256>(h.x + h.y + h.z + h.w, sbuf, &tot);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                if (ex < m && m <= ex + hs[i]) {
+                    spick[0] = 4 * tid + i;
+                    spick[1] = ex;
+                    spick[2] = ex + hs[i];
+                }
+                ex += hs[i];
+            }
+            __syncthreads();
+            const int pb = spick[0];
+            float blo, bhi;
+            extent([&](float v) { return v >= lo && v <= hi && bin(v) == pb; }, blo, bhi);
+            tau = bhi;
+            first = blo;
+            if (spick[2] <= m + 64) break;
+            below = spick[1];
+            lo = blo;
+            hi = bhi;
         }
-        __syncthreads();
-        prefix |= (uint32_t)sdig[0] << shift;
-        pmask |= 0xFFu << shift;
-        rem -= sdig[1];
-        __syncthreads();
+        ub = (double)tau + emax;
+        if (!ordered) sure = sure_below(first, emax);
     }
-    const double ub = (double)from_ord(prefix) + emax;
-
+    int32_t *orow = out + (int64_t)row * out_stride;
+    // written as "not above" so that a NaN approximation keeps the list as a candidate; the list's own
+    // bound is looked up only where the largest one passes
+    auto candidate = [&](int l, float v) {
+        return every || (!((double)v - emax > ub) && !((double)v - coarse_err(metric, d, bf, qn, cnorm[l]) > ub));
+    };
     int nk = 0, nb = 0;
     auto flush = [&]() {
         for (int e = tid; e < nb; e += 256) cd[e] = canon_dist(sx, cent + (int64_t)cl[e] * dpad, d, metric);
@@ -628,11 +804,8 @@ __global__ __launch_bounds__(256) void k_coarse_select(
             const double de = e < nk ? kd[e] : cd[e - nk];
             const int le = e < nk ? kl[e] : cl[e - nk];
             int rank = 0;
-            for (int f = 0; f < total; f++) {
-                const double df = f < nk ? kd[f] : cd[f - nk];
-                const int lf = f < nk ? kl[f] : cl[f - nk];
-                rank += (df < de) || (df == de && lf < le);
-            }
+            for (int f = 0; f < nk; f++) rank += (kd[f] < de) || (kd[f] == de && kl[f] < le);
+            for (int f = 0; f < nb; f++) rank += (cd[f] < de) || (cd[f] == de && cl[f] < le);
             if (rank < m) {
                 nd[rank] = de;
                 nl[rank] = le;
@@ -647,37 +820,38 @@ __global__ __launch_bounds__(256) void k_coarse_select(
         nb = 0;
         __syncthreads();
     };
-    for (int base = 0; base < nlist; base += 256) {
-        const int l = base + tid;
-        int isc = 0;
-        if (l < nlist) {
-            const double dv = (double)drow[l];
-            const double cn = cnorm[l];
-            const double el = coarse_err(metric, d, bf, qn, cn);
-            // written as "not above" so that a NaN approximation (or a NaN
-            // tau) keeps the list as a candidate
-            isc = (every || !(dv - el > ub)) ? 1 : 0;
+    // usually the candidates fit one re-check round: queued in any order (the ranking is by distance and id)
+    each([&](int l, float v) {
+        if (v < sure) {
+            orow[atomicAdd(&sdef, 1)] = l;
+        } else if (candidate(l, v)) {
+            const int at = atomicAdd(&scand, 1);
+            if (at < SEL_CAP) cl[at] = l;
         }
-        int tot;
-        const int pos = block_excl_scan<256>(isc, sbuf, &tot);
-        if (nb + tot > SEL_CAP) flush();
-        if (isc) cl[nb + pos] = l;
-        nb += tot;
-        __syncthreads();
+    });
+    __syncthreads();
+    const int ns = sdef;   // fewer than m
+    m -= ns;
+    if (scand <= SEL_CAP) {
+        nb = scand;
+        flush();
+    } else {
+        for (int base = 0; base < nlist; base += 256) {
+            const int l = base + tid;
+            const int isc = l < nlist && !(drow[l] < sure) && candidate(l, drow[l]) ? 1 : 0;
+            int tot;
+            const int pos = block_excl_scan<256>(isc, sbuf, &tot);
+            if (nb + tot > SEL_CAP) flush();
+            if (isc) cl[nb + pos] = l;
+            nb += tot;
+            __syncthreads();
+        }
+        flush();
     }
-    flush();
-    int32_t *orow = out + (int64_t)row * out_stride;
-    for (int p = tid; p < out_stride; p += 256) orow[p] = p < nk ? kl[p] : -1;
+    for (int p = tid; p < out_stride - ns; p += 256) orow[ns + p] = p < nk ? kl[p] : -1;
 }
 
-// The same selection for up to 2,048 lists and nprobe <= 64, one wave per
-// row and no block barrier: the row's approximate distances sit in registers
-// (lane l holds lists l + 64 i); tau, the m-th smallest, is found bit by bit
-// on their ordered keys (the key the radix select above finds); candidates
-// (the same test) are queued per wave in LDS and re-checked 64 at a time, each
-// batch merged into the row's best m -- sorted across the lanes by (exact
-// distance, list id) -- by a bitonic network.
-constexpr int SW_MAXL = 2048, SW_MAXM = 64, SW_Q = 128;
+constexpr int SW_Q = 128;   // queued candidates per wave
 
 __device__ __forceinline__ uint64_t ord64(double x) {
     const uint64_t b = (uint64_t)__double_as_longlong(x + 0.0);   // -0 ranks as +0
@@ -719,22 +893,40 @@ __device__ __forceinline__ void sel_sort64(uint64_t &k, int &l, bool asc) {
     for (int K = 2; K <= 64; K <<= 1) sel_clean(k, l, K, asc);
 }
 
-__global__ __launch_bounds__(256) void k_coarse_select_w(
+// The same selection, one wave per row and no block barrier: up to 2,048 lists
+// (NK = 16 or 32 distances per lane, list l + 64 i) and 128 probes (TWO: ranks
+// 64..127 in a second register).  The bound comes from a histogram as in
+// k_coarse_select, the wave's own, in LDS.  Candidates are queued per wave and
+// re-checked 64 at a time.  It is the better one for batches of SV_MINN rows or
+// more (four rows per block in flight): 10,000 rows x 1,024 lists, 32 probes, with
+// the GEMM, 101 against 129 us (a bisection of the keys' bits by ballots, before:
+// 145); 500 rows 26 against 24, one row 19 against 17.  With 64 distances per lane
+// (4,096 lists) the registers leave two waves per SIMD: 555 against 422 us for
+// 16,000 rows.
+constexpr int SV_BINS = 512, SV_MAXL = 2048, SV_MAXM = 128, SV_MINN = 1536;
+template <int NK, bool TWO>
+__global__ __launch_bounds__(256) void k_coarse_select_v(
     const float *__restrict__ dt, const float *__restrict__ X, int n, int d, const float *__restrict__ cent,
     int dpad, const double *__restrict__ cnorm, const double *__restrict__ cmax, int nlist, int metric,
     int m_uniform, const int32_t *__restrict__ m_per_row, int mmax, int32_t *__restrict__ out,
-    int out_stride, const int32_t *ctl, int gated, int bf) {
-    extern __shared__ __align__(16) unsigned char smem[];   // per wave: the row (dpad floats), then the queue
+    int out_stride, const int32_t *ctl, int gated, int bf, int ordered) {
+    extern __shared__ __align__(16) unsigned char smem[];   // per wave: the row (dpad floats)
+    __shared__ __align__(16) int shist[4][SV_BINS];
+    __shared__ int squeue[4][SW_Q];
     if (gated && call_failed(ctl)) return;
     const int lane = lane_id(), w = threadIdx.x >> 6;
     const int row = blockIdx.x * 4 + w;
     if (row >= n) return;   // whole waves only: this kernel has no block barrier
     float *sx = reinterpret_cast<float *>(smem) + w * dpad;
-    int *qu = reinterpret_cast<int *>(reinterpret_cast<float *>(smem) + 4 * dpad) + w * SW_Q;
+    int *qu = squeue[w], *hist = shist[w];
     int m = m_per_row ? m_per_row[row] : m_uniform;
     m = m < nlist ? m : nlist;
     m = m < mmax ? m : mmax;
     m = m < 1 ? 1 : m;
+    const float *drow = dt + (int64_t)row * nlist;
+    float key[NK];   // past the last list: +inf, above every bound
+#pragma unroll
+    for (int i = 0; i < NK; i++) key[i] = 64 * i + lane < nlist ? drow[64 * i + lane] : __builtin_inff();
     const float *xr = X + (int64_t)row * d;
     double q2 = 0.0;
     for (int j = lane; j < dpad; j += 64) {
@@ -747,29 +939,88 @@ __global__ __launch_bounds__(256) void k_coarse_select_w(
     const double cm = *cmax;
     const double emax = coarse_err(metric, d, bf, qn, cm);
     const bool every = !(qn + cm < 0x1p60);
-    const float *drow = dt + (int64_t)row * nlist;
-    uint32_t key[SW_MAXL / 64];
+    float lim = __builtin_inff();   // a list above it is no candidate (an upper bound of tau + 2 emax)
+    double ub = 0.0;
+    float sure = -__builtin_inff();   // lists below it are in the set (ordered = 0)
+    if (!every) {   // every distance is finite
+        float lo = __builtin_inff(), hi = -__builtin_inff();
 #pragma unroll
-    for (int i = 0; i < SW_MAXL / 64; i++) {
-        const int l = 64 * i + lane;
-        key[i] = l < nlist ? ord_bits(drow[l]) : 0xFFFFFFFFu;
-    }
-    // tau: the m-th smallest key, bit by bit (count(key < t) < m keeps bit b set); counts by ballot
-    const int ni = (nlist + 63) >> 6;
-    uint32_t t = 0;
-    for (int b = 31; b >= 0; b--) {
-        const uint32_t trial = t | (1u << b);
-        int c = 0;
+        for (int i = 0; i < NK; i++) {
+            lo = fminf(lo, key[i]);
+            if (64 * i + lane < nlist) hi = fmaxf(hi, key[i]);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o));
+            hi = fmaxf(hi, __shfl_xor(hi, o));
+        }
+        float tau = hi, first = lo;
+        int below = 0;   // lists under lo, all among the candidates
+        for (int round = 0; round < 3 && lo < hi; round++) {
+            const float range = hi - lo, scale = range > 0x1p-100f ? (SV_BINS - 1) / range : 0.f;
+            auto bin = [&](float v) { return min((int)((v - lo) * scale), SV_BINS - 1); };   // monotone in v
 #pragma unroll
-        for (int i = 0; i < SW_MAXL / 64; i++)
-            if (i < ni) c += (int)__builtin_popcountll(ballot(key[i] < trial));
-        if (c < m) t = trial;
+            for (int i = 0; i < SV_BINS / 256; i++)
+                *reinterpret_cast<int4 *>(&hist[4 * (lane + 64 * i)]) = make_int4(0, 0, 0, 0);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < NK; i++)
+                if (key[i] >= lo && key[i] <= hi) atomicAdd(&hist[bin(key[i])], 1);
+            __builtin_amdgcn_wave_barrier();
+            constexpr int B = SV_BINS / 64;   // consecutive bins per lane
+            int h[B], sum = 0;
+#pragma unroll
+            for (int i = 0; i < B; i += 4) {
+                const int4 v = *reinterpret_cast<const int4 *>(&hist[B * lane + i]);
+                h[i] = v.x;
+                h[i + 1] = v.y;
+                h[i + 2] = v.z;
+                h[i + 3] = v.w;
+                sum += v.x + v.y + v.z + v.w;
+            }
+            int ex = below + wave_incl_scan_dpp(sum) - sum;
+            const int src = __builtin_ctzll(ballot(ex < m && m <= ex + sum));   // the m-th smallest is in [lo, hi]
+            int pb = 0, pe = 0, pn = 0;   // its bin, the lists before and up to it
+#pragma unroll
+            for (int i = 0; i < B; i++) {
+                if (ex < m && m <= ex + h[i]) {
+                    pb = B * lane + i;
+                    pe = ex;
+                    pn = ex + h[i];
+                }
+                ex += h[i];
+            }
+            pb = readlane_i(pb, src);
+            pe = readlane_i(pe, src);
+            pn = readlane_i(pn, src);
+            float blo = __builtin_inff(), bhi = -__builtin_inff();
+#pragma unroll
+            for (int i = 0; i < NK; i++) {
+                if (key[i] >= lo && key[i] <= hi && bin(key[i]) == pb) {
+                    blo = fminf(blo, key[i]);
+                    bhi = fmaxf(bhi, key[i]);
+                }
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                blo = fminf(blo, __shfl_xor(blo, o));
+                bhi = fmaxf(bhi, __shfl_xor(bhi, o));
+            }
+            tau = bhi;
+            first = blo;
+            if (pn <= m + 32) break;
+            below = pe;
+            lo = blo;
+            hi = bhi;
+            __builtin_amdgcn_wave_barrier();
+        }
+        ub = (double)tau + emax;
+        // rounded up: the fp32 test admits every list that the fp64 test below does
+        lim = (float)(ub + emax);
+        lim += fabsf(lim) * 0x1p-22f + 0x1p-120f;
+        if (!ordered) sure = sure_below(first, emax);
     }
-    const double ub = (double)from_ord(t) + emax;
-    // the row's best m so far: rank r in lane r (empty: all ones)
-    uint64_t bk = ~0ull;
-    int bl = 0x7FFFFFFF;
-    int qn_ = 0;
+    int32_t *orow = out + (int64_t)row * out_stride;
+    uint64_t bk = ~0ull, bk2 = ~0ull;   // the row's best m so far: rank r in lane r, 64 + r in the second
+    int bl = 0x7FFFFFFF, bl2 = 0x7FFFFFFF, nq = 0;
     auto batch = [&](int c) {   // re-check queue[0, c) (c <= 64) and merge it in
         const int lc = lane < c ? qu[lane] : -1;
         uint64_t k = ~0ull;
@@ -780,44 +1031,59 @@ __global__ __launch_bounds__(256) void k_coarse_select_w(
         }
         sel_sort64(k, l, false);   // descending: the element-wise minimum with bk is bitonic
         if (lex_less(k, l, bk, bl)) {
+            const uint64_t tk = bk;
+            const int tl = bl;
             bk = k;
             bl = l;
+            k = tk;
+            l = tl;
         }
         sel_clean(bk, bl, 64, true);
-    };
-    // candidate test of every list first (all norm loads in flight together), then the queue
-    uint32_t cbits = 0;
-#pragma unroll
-    for (int i = 0; i < SW_MAXL / 64; i++) {
-        const int l = 64 * i + lane;
-        if (i < ni && l < nlist) {
-            const double dv = (double)from_ord(key[i]);
-            const double el = coarse_err(metric, d, bf, qn, cnorm[l]);
-            cbits |= (every || !(dv - el > ub)) ? (1u << i) : 0u;   // "not above": a NaN keeps the list
-        }
-    }
-    for (int i = 0; i < ni; i++) {
-        const int l = 64 * i + lane;
-        const bool isc = (cbits >> i) & 1u;
-        const uint64_t bm = ballot(isc);
-        if (bm) {
-            if (isc) qu[qn_ + (int)__builtin_popcountll(bm & lanemask_lt())] = l;
-            qn_ += (int)__builtin_popcountll(bm);
-            __builtin_amdgcn_wave_barrier();
-            if (qn_ >= 64) {
-                batch(64);
-                const int rest = qn_ - 64;
-                const int v = lane < rest ? qu[64 + lane] : 0;
-                __builtin_amdgcn_wave_barrier();
-                if (lane < rest) qu[lane] = v;
-                __builtin_amdgcn_wave_barrier();
-                qn_ = rest;
+        if (TWO) {   // the 64 larger ones against ranks 64..127
+            sel_clean(k, l, 64, false);
+            if (lex_less(k, l, bk2, bl2)) {
+                bk2 = k;
+                bl2 = l;
             }
+            sel_clean(bk2, bl2, 64, true);
+        }
+    };
+    uint64_t cand = 0;   // bit i: list 64 i + lane passes the coarse test ("not above": a NaN keeps the list)
+    int ns = 0;          // lists certainly in the set, fewer than m
+#pragma unroll
+    for (int i = 0; i < NK; i++) {
+        const bool in = key[i] < sure;
+        const uint64_t im = ballot(in);
+        if (in) orow[ns + (int)__builtin_popcountll(im & lanemask_lt())] = 64 * i + lane;
+        ns += (int)__builtin_popcountll(im);
+        cand |= (uint64_t)(64 * i + lane < nlist && !in && !(key[i] > lim) ? 1 : 0) << i;
+    }
+    m -= ns;
+    for (int i = 0; i < NK; i++) {
+        bool isc = (cand >> i) & 1ull;
+        if (!ballot(isc)) continue;
+        const int l = 64 * i + lane;
+        // the list's own bound, where the largest one passes
+        if (isc && !every) isc = !((double)drow[l] - coarse_err(metric, d, bf, qn, cnorm[l]) > ub);
+        const uint64_t bm = ballot(isc);
+        if (isc) qu[nq + (int)__builtin_popcountll(bm & lanemask_lt())] = l;
+        nq += (int)__builtin_popcountll(bm);
+        __builtin_amdgcn_wave_barrier();
+        if (nq >= 64) {
+            batch(64);
+            const int rest = nq - 64;
+            const int v = lane < rest ? qu[64 + lane] : 0;
+            __builtin_amdgcn_wave_barrier();
+            if (lane < rest) qu[lane] = v;
+            __builtin_amdgcn_wave_barrier();
+            nq = rest;
         }
     }
-    if (qn_ > 0) batch(qn_);
-    int32_t *orow = out + (int64_t)row * out_stride;
-    for (int p = lane; p < out_stride; p += 64) orow[p] = (p < m && bl != 0x7FFFFFFF) ? bl : -1;
+    if (nq > 0) batch(nq);
+    for (int p = lane; p < out_stride - ns; p += 64) {
+        const int l = p < 64 ? bl : bl2;   // p >= 64 only in the second round of the loop and later
+        orow[ns + p] = (p < m && l != 0x7FFFFFFF) ? l : -1;
+    }
 }
 
 // Nearest list per row (m = 1) from the group minima of k_coarse_gemm<.., 1>.
@@ -976,10 +1242,36 @@ static void coarse_gemm_t(hipStream_t st, const float *X, int n, int d, const fl
 #undef SIVF_GEMM
 }
 
+// Tiles of 128 x 128 below which the untiled kernel computes the distances (a
+// tile per CU; 256 CUs).
+constexpr int SMALL_TILES = 256;
+
 void launch_coarse_gemm(hipStream_t st, const float *X, int n, int d, const float *cent, const uint16_t *cent_h, int dpad,
                         const float *cn2, int nlist, int metric, float *out, const int32_t *ctl,
                         int gated, int bf) {
-    if (n > 0) coarse_gemm_t<0>(st, X, n, d, cent, cent_h, dpad, cn2, nlist, metric, out, nullptr, nlist, ctl, gated, bf);
+    if (n <= 0) return;
+    const int64_t tiles = (int64_t)((n + GM - 1) / GM) * ((nlist + GN - 1) / GN);
+    if (bf || tiles >= SMALL_TILES) {
+        coarse_gemm_t<0>(st, X, n, d, cent, cent_h, dpad, cn2, nlist, metric, out, nullptr, nlist, ctl, gated, bf);
+        return;
+    }
+    const bool vec = (d % 4 == 0) && (((uintptr_t)X & 15) == 0);
+    const int lt = (int64_t)((n + 15) / 16) * ((nlist + 31) / 32) < 1024 ? 1 : 2;
+    const unsigned grid = (unsigned)(((n + 15) / 16) * ((nlist + 64 * lt - 1) / (64 * lt)));
+#define SIVF_SMALL(M, V, L)                                                                                   \
+    hipLaunchKernelGGL((k_coarse_small<M, V, L>), dim3(grid), dim3(256), 0, st, X, n, d, cent, dpad, cn2, nlist, out, \
+                       ctl, gated)
+#define SIVF_SMALL_L(M, V)                                                                                    \
+    do {                                                                                                      \
+        if (lt == 1) SIVF_SMALL(M, V, 1); else SIVF_SMALL(M, V, 2);                                           \
+    } while (0)
+    if (metric == 0) {
+        if (vec) SIVF_SMALL_L(0, true); else SIVF_SMALL_L(0, false);
+    } else {
+        if (vec) SIVF_SMALL_L(1, true); else SIVF_SMALL_L(1, false);
+    }
+#undef SIVF_SMALL_L
+#undef SIVF_SMALL
 }
 
 int coarse_groups(int nlist) { return (nlist + GROUP - 1) / GROUP; }
@@ -1043,18 +1335,32 @@ void launch_coarse_assign(hipStream_t st, float *scratch, const float *X, int n,
 void launch_coarse_select(hipStream_t st, const float *dt, const float *X, int n, int d, const float *cent,
                           int dpad, const double *cnorm, const double *cmax, int nlist, int metric,
                           int m_uniform, const int32_t *m_per_row, int mmax, int32_t *out, int out_stride,
-                          const int32_t *ctl, int gated, int bf) {
+                          const int32_t *ctl, int gated, int bf, int ordered) {
     if (n <= 0) return;
-    if (nlist <= SW_MAXL && mmax <= SW_MAXM) {
-        hipLaunchKernelGGL(k_coarse_select_w, dim3((n + 3) / 4), dim3(256),
-                           (size_t)4 * dpad * sizeof(float) + (size_t)4 * SW_Q * sizeof(int), st, dt, X, n, d, cent,
-                           dpad, cnorm, cmax, nlist, metric, m_uniform, m_per_row, mmax, out, out_stride, ctl, gated,
-                           bf);
+    if (n >= SV_MINN && nlist <= SV_MAXL && mmax <= SV_MAXM) {
+#define SIVF_SELV(NK, TWO)                                                                                    \
+    hipLaunchKernelGGL((k_coarse_select_v<NK, TWO>), dim3((n + 3) / 4), dim3(256), (size_t)4 * dpad * sizeof(float), \
+                       st, dt, X, n, d, cent, dpad, cnorm, cmax, nlist, metric, m_uniform, m_per_row, mmax, out,    \
+                       out_stride, ctl, gated, bf, ordered)
+#define SIVF_SELV_M(NK)                                                                                       \
+    do {                                                                                                      \
+        if (mmax <= 64) SIVF_SELV(NK, false); else SIVF_SELV(NK, true);                                       \
+    } while (0)
+        if (nlist <= 1024) SIVF_SELV_M(16); else SIVF_SELV_M(32);
+#undef SIVF_SELV_M
+#undef SIVF_SELV
         return;
     }
-    hipLaunchKernelGGL(k_coarse_select, dim3(n), dim3(256), coarse_select_smem(dpad, mmax), st, dt, X, n, d,
-                       cent, dpad, cnorm, cmax, nlist, metric, m_uniform, m_per_row, mmax, out, out_stride,
-                       ctl, gated, bf);
+#define SIVF_SELECT(NK)                                                                                       \
+    hipLaunchKernelGGL(k_coarse_select<NK>, dim3(n), dim3(256), coarse_select_smem(dpad, mmax), st, dt, X, n, d, \
+                       cent, dpad, cnorm, cmax, nlist, metric, m_uniform, m_per_row, mmax, out, out_stride,      \
+                       ctl, gated, bf, ordered)
+    if (nlist <= 1024) SIVF_SELECT(4);
+    else if (nlist <= 2048) SIVF_SELECT(8);
+    else if (nlist <= 4096) SIVF_SELECT(16);
+    else if (nlist <= 16384) SIVF_SELECT(64);
+    else SIVF_SELECT(0);
+#undef SIVF_SELECT
 }
 
 }  // namespace sivf

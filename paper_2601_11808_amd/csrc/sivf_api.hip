@@ -236,7 +236,7 @@ void prof_end(sivf_index *ix, int kind, int slot, hipStream_t st) {
 
 // Coarse selection over rows [0, n) in chunks that fit the scratch.
 void coarse(sivf_index *ix, hipStream_t st, float *dt, const float *x, int64_t n, int m, const int32_t *m_per_row,
-            int mmax, int32_t *out, int out_stride, int gated) {
+            int mmax, int32_t *out, int out_stride, int gated, int ordered = 1) {
     const Dev &S = ix->S;
     const int dpad = S.dp4 * 4;
     // inserts are assigned on bf16 MFMA (every storage): the nearest list is almost always separated
@@ -260,7 +260,7 @@ void coarse(sivf_index *ix, hipStream_t st, float *dt, const float *x, int64_t n
         launch_coarse_gemm(st, xr, nr, S.d, S.cent, S.cent_h, dpad, S.cn2, S.nlist, S.metric, dt, S.ctl, gated, bf);
         launch_coarse_select(st, dt, xr, nr, S.d, S.cent, dpad, S.cnorm, S.cmax, S.nlist, S.metric, m,
                              m_per_row ? m_per_row + r0 : nullptr, mmax, out + r0 * out_stride, out_stride,
-                             S.ctl, gated, bf);
+                             S.ctl, gated, bf, ordered);
     }
 }
 
@@ -316,7 +316,7 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     const int stride = mmax < c.nlist ? mmax : c.nlist;
     const int ps = prof_begin(ix, SIVF_PROF_SEARCH, st);
     const int pc = prof_begin(ix, SIVF_PROF_COARSE, st);
-    coarse(ix, st, ix->dt_s, q, nq, npq ? 0 : stride, npq, stride, ix->W.probes, stride, 0);
+    coarse(ix, st, ix->dt_s, q, nq, npq ? 0 : stride, npq, stride, ix->W.probes, stride, 0, 0);
     prof_end(ix, SIVF_PROF_COARSE, pc, st);
     if (c.storage != SIVF_F32) {
         const KClass all = kclass_all(stride);

@@ -24,10 +24,11 @@ int coarse_assign_words(int nlist, int dpad);
 void launch_coarse_assign(hipStream_t st, float *scratch, const float *X, int n, int d, const float *cent,
                           const uint16_t *cent_h, int dpad, const float *cn2, const double *cmax, int nlist, int metric, int32_t *out,
                           int out_stride, const int32_t *ctl, int gated, int bf);
+// ordered: the m lists of a row nearest first; 0: the same lists in any order
 void launch_coarse_select(hipStream_t st, const float *dt, const float *X, int n, int d, const float *cent,
                           int dpad, const double *cnorm, const double *cmax, int nlist, int metric,
                           int m_uniform, const int32_t *m_per_row, int mmax, int32_t *out, int out_stride,
-                          const int32_t *ctl, int gated, int bf);
+                          const int32_t *ctl, int gated, int bf, int ordered);
 
 // ---- mutation (mutate.hip)
 struct Batch {

@@ -67,3 +67,32 @@ def test_few_queries_small_buffers():
         assert ix.sync() == 0
         st, rd, rl = ref.search(q[:1], k, 8)
         assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
+
+
+# the selection kernels' edges: lists per thread (1,024 / 2,048 / 4,096 / 16,384 and past them), rows per launch
+# (the wave kernel from 1,536 rows), probes 64 / 65 / 128 / 129, and the untiled GEMM's ragged last lists
+@pytest.mark.parametrize("nlist,nq,nprobe", [(17, 3, 17), (1024, 5, 64), (1023, 1536, 64), (1025, 1536, 65),
+                                             (2048, 1540, 128), (2048, 1536, 129), (2049, 40, 33), (4097, 7, 128),
+                                             (16384, 3, 64), (16400, 3, 200)])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_probe_selection_edges(nlist, nq, nprobe, metric):
+    """Probes in order, and a search over the unordered set, equal the oracle's; centroids repeat (exact ties)
+    and a query equals one."""
+    rng = np.random.default_rng([23, nlist, nprobe, metric])
+    d = 24
+    cent = rng.integers(-4, 5, (nlist, d)).astype(np.float32)
+    cent[nlist // 2] = cent[0]
+    q = rng.integers(-4, 5, (nq, d)).astype(np.float32)
+    q[0] = cent[0]
+    x = rng.integers(-4, 5, (4000, d)).astype(np.float32)
+    slabs = 4000 // 4 + nlist + 8
+    ix = sivf.Index(d, nlist, cent, metric=metric, slab_capacity=4, num_slabs=slabs, id_capacity=4000, max_batch=4000,
+                    max_queries=2000, max_k=16, max_nprobe=200)
+    ref = oracle.OracleIndex(d, nlist, cent, metric, 4, slabs, 4000)
+    ix.add(x, np.arange(4000))
+    assert ix.sync() == 0 and ref.add(x, np.arange(4000)) == 0
+    np.testing.assert_array_equal(ix.probe(q, nprobe).cpu().numpy(), oracle.probe(q, cent, nprobe, metric))
+    gd, gl = ix.search(q, 7, nprobe)
+    assert ix.sync() == 0
+    st, rd, rl = ref.search(q, 7, nprobe)
+    assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
