@@ -427,12 +427,21 @@ __global__ __launch_bounds__(1024) void k_rm_plan(Dev S, int64_t *n_removed, int
 }
 
 // Holes: deleted positions below the new length n' of their list.  The h-th
-// hole of list l (in any order) is stored at seg[l_off[l] + h].
+// hole of list l (in any order) is stored at seg[l_off[l] + h].  The blocks past
+// the first nb map the tail-window entries to their lists for the move: entries
+// l_off[l] .. +l_m[l] belong to list l (one wave per list).
 template <bool BLK>
-__global__ __launch_bounds__(256) void k_rm_holes(Dev S, int n, const uint32_t *__restrict__ rec,
-                                                  int32_t *__restrict__ seg, int mode) {
+__global__ __launch_bounds__(256) void k_rm_holes(Dev S, int n, int nb, const uint32_t *__restrict__ rec,
+                                                  int32_t *__restrict__ seg, int32_t *__restrict__ emap, int mode) {
     extern __shared__ int32_t hist[];
     if (rm_skip(S, mode)) return;
+    if ((int)blockIdx.x >= nb) {
+        const int l = ((int)blockIdx.x - nb) * 4 + (threadIdx.x >> 6);
+        if (l >= S.nlist) return;
+        const int m = S.l_m[l], o = S.l_off[l];
+        for (int j = lane_id(); j < m; j += 64) emap[o + j] = l;
+        return;
+    }
     const int i = blockIdx.x * 256 + threadIdx.x;
     const uint32_t g = i < n ? rec[i] : INVALID;
     const bool hit = g != INVALID;
@@ -447,8 +456,6 @@ __global__ __launch_bounds__(256) void k_rm_holes(Dev S, int n, const uint32_t *
     if (hole) seg[S.l_off[l] + h] = (int32_t)g;
 }
 
-// Tail-window entry -> list map for the move: entries l_off[l] .. +l_m[l]
-// belong to list l.  One wave per list.
 __global__ __launch_bounds__(256) void k_rm_expand(Dev S, int32_t *__restrict__ emap, int mode) {
     if (rm_skip(S, mode)) return;
     const int l = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -457,20 +464,37 @@ __global__ __launch_bounds__(256) void k_rm_expand(Dev S, int32_t *__restrict__ 
     for (int j = lane_id(); j < m; j += 64) emap[o + j] = l;
 }
 
+// Distinct increments of counters[key] for the active lanes of a wave whose
+// equal keys are adjacent: one atomic per run of lanes, all of them in one
+// instruction.  (One returning atomic after another, a list at a time, took 40 us
+// for 1,000 entries of 1,000 lists.)  Every lane of the wave must call it.
+__device__ __forceinline__ int wave_run_inc(int32_t *counters, int key, bool active) {
+    const int lane = lane_id();
+    const bool head = lane == 0 || __shfl_up(key, 1) != key;
+    const uint64_t heads = ballot(head), act = ballot(active);
+    const uint64_t upto = lanemask_lt() | (1ull << lane);
+    const int first = 63 - (int)__builtin_clzll(heads & upto);
+    const uint64_t after = heads & ~upto;
+    const int next = after ? (int)__builtin_ctzll(after) : 64;
+    const uint64_t run = (next == 64 ? ~0ull : ((1ull << next) - 1)) & (~0ull << first);
+    int base = 0;
+    if (head && (act & run)) base = atomicAdd(&counters[key], (int)__builtin_popcountll(act & run));
+    return __shfl(base, first) + (int)__builtin_popcountll(act & run & lanemask_lt());
+}
+
 // The tail windows [n', n) of all lists with deletions, list after list, one
 // lane per position (the window of list l has l_m[l] positions and starts at
 // entry l_off[l]).  A position that still holds a live entry is a survivor;
-// the r-th survivor of a list moves into its r-th hole.  Consecutive lanes
-// read consecutive slots, so each 16-byte dimension chunk of a wave's
-// survivors is one contiguous read; the holes they fill are scattered.
-template <bool HALF>
-__global__ __launch_bounds__(256) void k_rm_move(Dev S, int n, const int32_t *__restrict__ seg,
-                                                 const int32_t *__restrict__ emap, int mode) {
+// the r-th survivor of a list moves into its r-th hole.  Entry e's move goes to
+// src[e] (in place of its list in emap) and dst[e]; no survivor: dst[e] = INVALID.
+__global__ __launch_bounds__(256) void k_rm_resolve(Dev S, const int32_t *__restrict__ seg, int32_t *emap,
+                                                    uint32_t *__restrict__ dst, int mode) {
     if (rm_skip(S, mode)) return;
     const int e = blockIdx.x * 256 + threadIdx.x;
     const int total = S.ctl[CTL_RMTOT];
+    if (blockIdx.x * 256 >= total) return;
     const bool active = e < total;
-    const int l = active ? emap[e] : 0;
+    const int l = active ? emap[e] : -1;
     uint32_t src = 0, id = INVALID;
     if (active) {
         const int tp = S.l_newlen[l] + (e - S.l_off[l]);
@@ -481,26 +505,50 @@ __global__ __launch_bounds__(256) void k_rm_move(Dev S, int n, const int32_t *__
             id = INVALID;
     }
     const bool surv = id != INVALID;
-    const int r = wave_agg_inc(S.l_s, l, surv);
-    if (!surv) return;
-    const uint32_t dst = (uint32_t)seg[S.l_off[l] + r];
+    const int r = wave_run_inc(S.l_s, l, surv);
+    if (active) {
+        dst[e] = surv ? (uint32_t)seg[S.l_off[l] + r] : INVALID;
+        emap[e] = (int32_t)src;
+    }
+}
+
+// Move the survivors: one lane per entry and group of MV_CH 16-byte chunks
+// (blockIdx.y).  Consecutive lanes read consecutive slots, so each chunk of a
+// wave's survivors is one contiguous read; the holes they fill are scattered.  What
+// bounds it is those writes (16 of a line's 128 bytes; the L2 merges neighbours
+// where it can); a group of 8 chunks keeps all its loads in flight in 32 registers,
+// and wide rows and small batches spread over more blocks (5,000 rows of 240
+// chunks, one lane per row: 112 us).
+constexpr int MV_CH = 8;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool HALF>
+__global__ __launch_bounds__(256) void k_rm_move(Dev S, const int32_t *__restrict__ from,
+                                                 const uint32_t *__restrict__ to, int mode) {
+    if (rm_skip(S, mode)) return;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= S.ctl[CTL_RMTOT]) return;
+    const uint32_t dst = to[e], src = (uint32_t)from[e];
+    if (dst == INVALID) return;
     const int64_t ss = (int64_t)(src / S.C), sl = src % S.C, ds = (int64_t)(dst / S.C), dl = dst % S.C;
-    const float4 *sp = S.data + ss * S.dp4 * S.C + sl;
-    float4 *dp = S.data + ds * S.dp4 * S.C + dl;
-    int c = 0;
-    for (; c + 16 <= S.dp4; c += 16) {   // 16 chunks of the row in flight
-        float4 v[16];
+    const int g0 = blockIdx.y * MV_CH;
+    // one 16-byte chunk layout for both copies (arrays of float4 here ended in scratch memory)
+    auto copy = [&](const void *base_s, void *base_d, int nch) {
+        const u32x4 *sp = static_cast<const u32x4 *>(base_s) + ss * nch * S.C + sl;
+        u32x4 *dp = static_cast<u32x4 *>(base_d) + ds * nch * S.C + dl;
+        if (g0 + MV_CH <= nch) {
+            u32x4 v[MV_CH];
 #pragma unroll
-        for (int j = 0; j < 16; j++) v[j] = sp[(int64_t)(c + j) * S.C];
+            for (int j = 0; j < MV_CH; j++) v[j] = sp[(int64_t)(g0 + j) * S.C];
 #pragma unroll
-        for (int j = 0; j < 16; j++) dp[(int64_t)(c + j) * S.C] = v[j];
-    }
-    for (; c < S.dp4; c++) dp[(int64_t)c * S.C] = sp[(int64_t)c * S.C];
-    if (HALF) {
-        const uint4 *hs = S.hdata + ss * S.dp8 * S.C + sl;
-        uint4 *hd = S.hdata + ds * S.dp8 * S.C + dl;
-        for (int c8 = 0; c8 < S.dp8; c8++) hd[(int64_t)c8 * S.C] = hs[(int64_t)c8 * S.C];
-    }
+            for (int j = 0; j < MV_CH; j++) dp[(int64_t)(g0 + j) * S.C] = v[j];
+        } else {
+            for (int c = g0; c < nch; c++) dp[(int64_t)c * S.C] = sp[(int64_t)c * S.C];
+        }
+    };
+    copy(S.data, S.data, S.dp4);
+    if (HALF) copy(S.hdata, S.hdata, S.dp8);   // dp8 <= dp4: the groups cover it
+    if (blockIdx.y) return;
+    const uint32_t id = S.sids[src];
     if (S.xnorm) S.xnorm[dst] = S.xnorm[src];
     S.sids[dst] = id;
     S.att[id] = dst;
@@ -651,7 +699,7 @@ __global__ __launch_bounds__(256) void k_cmp_tail(Dev S, const int32_t *__restri
         const int slab = slab_of(S, l, tp / S.C), slot = tp % S.C;
         dead = !((S.bits[(int64_t)slab * S.bw + (slot >> 6)] >> (slot & 63)) & 1ull);
     }
-    wave_agg_inc(S.l_q, l, dead);
+    wave_run_inc(S.l_q, l, dead);   // entries are in list order
 }
 
 // Holes: dead slots below n'.  A compacted list needs one per survivor of its
@@ -858,16 +906,20 @@ void launch_add_cleanup(hipStream_t st, const Dev &S, int n, const int64_t *ids)
     hipLaunchKernelGGL(k_add_cleanup, dim3(blocks(n)), dim3(256), 0, st, S, n, ids);
 }
 
+// Survivors of at most n tail-window entries into their holes (B.inv: each entry's list; B.rec is free by now).
+static void launch_move(hipStream_t st, const Dev &S, int n, const Batch &B, int mode) {
+    hipLaunchKernelGGL(k_rm_resolve, dim3(blocks(n)), dim3(256), 0, st, S, B.seg, B.inv, B.rec, mode);
+    const dim3 grid(blocks(n), (unsigned)((S.dp4 + MV_CH - 1) / MV_CH));
+    if (S.storage != 0) hipLaunchKernelGGL(k_rm_move<true>, grid, dim3(256), 0, st, S, B.inv, B.rec, mode);
+    else hipLaunchKernelGGL(k_rm_move<false>, grid, dim3(256), 0, st, S, B.inv, B.rec, mode);
+}
+
 void launch_remove(hipStream_t st, const Dev &S, int n, const int64_t *ids, int64_t *n_removed, const Batch &B, int mode) {
     if (mode == 0) hipLaunchKernelGGL(k_rm_validate, dim3(blocks(n)), dim3(256), 0, st, S, n, ids);
     SIVF_LAUNCH_BLK(k_rm_mark, blocks(n), st, S, n, ids, B.rec, mode);
     hipLaunchKernelGGL(k_rm_plan, dim3(1), dim3(1024), 0, st, S, n_removed, mode);
-    SIVF_LAUNCH_BLK(k_rm_holes, blocks(n), st, S, n, B.rec, B.seg, mode);
-    hipLaunchKernelGGL(k_rm_expand, dim3(blocks(S.nlist, 4)), dim3(256), 0, st, S, B.inv, mode);
-    if (S.storage != 0)
-        hipLaunchKernelGGL(k_rm_move<true>, dim3(blocks(n)), dim3(256), 0, st, S, n, B.seg, B.inv, mode);
-    else
-        hipLaunchKernelGGL(k_rm_move<false>, dim3(blocks(n)), dim3(256), 0, st, S, n, B.seg, B.inv, mode);
+    SIVF_LAUNCH_BLK(k_rm_holes, blocks(n) + blocks(S.nlist, 4), st, S, n, (int)blocks(n), B.rec, B.seg, B.inv, mode);
+    launch_move(st, S, n, B, mode);
     hipLaunchKernelGGL(k_rm_finalize, dim3(blocks(S.nlist)), dim3(256), 0, st, S, mode);
 }
 
@@ -884,10 +936,7 @@ void launch_compact(hipStream_t st, const Dev &S, float min_dead_fraction, int b
     hipLaunchKernelGGL(k_rm_expand, dim3(blocks(S.nlist, 4)), dim3(256), 0, st, S, B.inv, 0);
     hipLaunchKernelGGL(k_cmp_tail, dim3(blocks(budget)), dim3(256), 0, st, S, B.inv);
     hipLaunchKernelGGL(k_cmp_holes, dim3(blocks(S.num_slabs)), dim3(256), 0, st, S, B.seg);
-    if (S.storage != 0)
-        hipLaunchKernelGGL(k_rm_move<true>, dim3(blocks(budget)), dim3(256), 0, st, S, budget, B.seg, B.inv, 0);
-    else
-        hipLaunchKernelGGL(k_rm_move<false>, dim3(blocks(budget)), dim3(256), 0, st, S, budget, B.seg, B.inv, 0);
+    launch_move(st, S, budget, B, 0);
     hipLaunchKernelGGL(k_rm_finalize, dim3(blocks(S.nlist)), dim3(256), 0, st, S, 0);
 }
 

@@ -96,3 +96,33 @@ def test_probe_selection_edges(nlist, nq, nprobe, metric):
     assert ix.sync() == 0
     st, rd, rl = ref.search(q, 7, nprobe)
     assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
+
+
+# the move of survivors: groups of 8 chunks (d past 32 and 64), runs of lists shorter and longer than a wave, and a
+# whole list
+@pytest.mark.parametrize("d,C,storage", [(5, 4, 0), (33, 64, 0), (72, 32, 1), (260, 16, 0)])
+def test_delete_moves(d, C, storage):
+    rng = np.random.default_rng([24, d])
+    sizes = [700, 1, 2, 3, 300, 0] + [5] * 90
+    nlist, n = len(sizes), sum(sizes)
+    cent = (rng.standard_normal((nlist, d)) * 8).astype(np.float32)
+    x = (cent[np.repeat(np.arange(nlist), sizes)] + rng.standard_normal((n, d))).astype(np.float32)
+    ids = rng.permutation(n)
+    slabs = n // C + 2 * nlist
+    ix = sivf.Index(d, nlist, cent, slab_capacity=C, num_slabs=slabs, id_capacity=n, max_batch=n, max_queries=16,
+                    max_k=16, max_nprobe=16, storage=storage, rerank_factor=4 if storage else 0)
+    ref = oracle.OracleIndex(d, nlist, cent, 0, C, slabs, n)
+    ix.add(x, ids)
+    assert ix.sync() == 0 and ref.add(x, ids) == 0
+    row_of = np.argsort(ids)
+    for share in (0.02, 0.3, 0.5, 1.0):
+        live = ref.live_ids() if hasattr(ref, "live_ids") else np.concatenate(list(ref.membership().values()))
+        rm = rng.choice(live, max(1, int(share * live.shape[0])), replace=False).astype(np.int64)
+        nr = ix.remove(rm)
+        assert ix.sync() == 0 and int(nr.item()) == rm.shape[0]
+        assert ref.remove(rm)[0] == 0
+        gm, om = ix.membership(), ref.membership()
+        assert gm.keys() == om.keys() and all(np.array_equal(gm[l], np.sort(om[l])) for l in om)
+        keep = np.setdiff1d(live, rm)
+        if keep.shape[0]:
+            np.testing.assert_array_equal(ix.get_rows(keep).cpu().numpy(), x[row_of[keep]])
