@@ -23,7 +23,7 @@ LIB = os.path.join(PKG, "libsivf.so")
 ARCH = "gfx950"
 
 SOURCES = ["sivf_api.hip", "setup.hip", "coarse.hip", "mutate.hip", "search.hip", "scan_mfma.hip",
-           "serve.hip", "registry.hip"]
+           "scan_cert_l2.hip", "scan_cert_ip.hip", "serve.hip", "registry.hip"]
 
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

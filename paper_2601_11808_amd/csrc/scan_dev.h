@@ -233,6 +233,25 @@ __device__ __forceinline__ int query_k(const int32_t *kpq, int k, int qi) {
     return kq < 0 ? 0 : (kq > k ? k : kq);
 }
 
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int DT>
+__device__ __forceinline__ f32x4_t mfma_16x16x32(uint4 a, uint4 b, f32x4_t c) {
+    if constexpr (DT == 1)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                      c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b),
+                                                     c, 0, 0, 0);
+}
+
+constexpr int MQ = 16;       // queries per MFMA tile
+constexpr int MKB = 8;       // k-blocks of 32 dims: d <= 256
+constexpr int MBUF = 96;     // candidate buffer per query (a step adds at most 64)
+
+
 // Work items of a call without splitting: tiles of T pairs per list.  The
 // plan may split long lists until the items reach twice this, or twice what
 // fills the chip (or the buffer); the dispatch grid covers that bound.

@@ -822,7 +822,8 @@ void launch_search_scan(hipStream_t st, const Dev &S, const SearchBufs &W, int n
     const int T = search_tile(S);
     const int npairs = nq * np_stride;
     if (T == 16) {   // the schedule setter admits tile 16 only where cert_ok holds
-        launch_scan_cert(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        if (S.metric == 0) launch_scan_cert_l2(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
+        else launch_scan_cert_ip(st, S, W, q, np_stride, kcap, k, k_per_query, npairs);
         return;
     }
     if (kcap > 64) {

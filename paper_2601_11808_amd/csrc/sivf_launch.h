@@ -107,9 +107,11 @@ void launch_search_plan(hipStream_t st, const Dev &S, const SearchBufs &W, int n
                         int32_t *heat = nullptr);
 void launch_search_scan(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const float *q, int np_stride,
                         int kcap, int k, const int32_t *k_per_query);
-// its certified matrix-core form (tile 16)
-void launch_scan_cert(hipStream_t st, const Dev &S, const SearchBufs &W, const float *q, int np_stride, int kcap,
-                      int k, const int32_t *k_per_query, int npairs);
+// its certified matrix-core form (tile 16), per metric
+void launch_scan_cert_l2(hipStream_t st, const Dev &S, const SearchBufs &W, const float *q, int np_stride, int kcap, int k,
+                         const int32_t *k_per_query, int npairs);
+void launch_scan_cert_ip(hipStream_t st, const Dev &S, const SearchBufs &W, const float *q, int np_stride, int kcap, int k,
+                         const int32_t *k_per_query, int npairs);
 // prior (or NULL): per query, prior_stride sorted keys merged in as one more source;
 // keys_out (or NULL): sorted keys (stride out_stride) instead of dist / labels
 void launch_search_merge(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const KClass &cls, int kcap,
