@@ -654,7 +654,8 @@ constexpr int SEL_BINS = 1024;
 // ordered = 0 (a search needs the probe set, not its order): no exact m-th
 // distance is below the smallest distance of that bin by more than max E, so a
 // list below it by more than 2 max E is in the set without an exact distance, and
-// only the lists around the bin are re-checked.  The re-check reads one
+// only the lists around the bin are re-checked.  The nearest list still comes
+// first: a large search scans it before the others.  The re-check reads one
 // centroid row per lane (16 bytes of 64 lines per load) and took most of the time.
 // Dynamic shared memory:
 //   sx[dpad] float | kd[mmax] kl[mmax] nd[mmax] nl[mmax] | cd[SEL_CAP] cl[SEL_CAP]
@@ -670,7 +671,7 @@ __global__ __launch_bounds__(256, NK <= 16 ? 6 : 1) void k_coarse_select(
     __shared__ double sred[4];
     __shared__ float sext[2][4];
     __shared__ int spick[3];
-    __shared__ int scand, sdef;
+    __shared__ int scand, sdef, snear;
     if (gated && call_failed(ctl)) return;
     const int row = blockIdx.x;
     if (row >= n) return;
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(256, NK <= 16 ? 6 : 1) void k_coarse_select(
     }
     for (int o = 32; o > 0; o >>= 1) q2 += __shfl_xor(q2, o);
     if (lane == 0) sred[w] = q2;
-    if (tid == 0) scand = sdef = 0;
+    if (tid == 0) scand = sdef = snear = 0;
     __syncthreads();
     const double qn = sqrt(sred[0] + sred[1] + sred[2] + sred[3]) * (1.0 + 0x1p-50);
     const double cm = *cmax;
@@ -747,9 +748,11 @@ __global__ __launch_bounds__(256, NK <= 16 ? 6 : 1) void k_coarse_select(
     };
     double ub = 0.0;
     float sure = -__builtin_inff();   // lists below it are in the set
+    float nearest = -__builtin_inff();
     if (!every) {
         float lo, hi;
         extent([](float) { return true; }, lo, hi);
+        nearest = lo;
         int below = 0;   // lists under lo, all among the candidates
         float tau = hi, first = lo;
         for (int round = 0; round < 3 && lo < hi; round++) {
@@ -822,15 +825,15 @@ __global__ __launch_bounds__(256, NK <= 16 ? 6 : 1) void k_coarse_select(
     };
     // usually the candidates fit one re-check round: queued in any order (the ranking is by distance and id)
     each([&](int l, float v) {
-        if (v < sure) {
-            orow[atomicAdd(&sdef, 1)] = l;
+        if (v < sure) {   // a nearest list first (when it is one of these), the others in any order behind it
+            orow[v == nearest && atomicExch(&snear, 1) == 0 ? 0 : 1 + atomicAdd(&sdef, 1)] = l;
         } else if (candidate(l, v)) {
             const int at = atomicAdd(&scand, 1);
             if (at < SEL_CAP) cl[at] = l;
         }
     });
     __syncthreads();
-    const int ns = sdef;   // fewer than m
+    const int ns = sdef + snear;   // fewer than m; the nearest list is among them if any is
     m -= ns;
     if (scand <= SEL_CAP) {
         nb = scand;
@@ -942,6 +945,7 @@ __global__ __launch_bounds__(256) void k_coarse_select_v(
     float lim = __builtin_inff();   // a list above it is no candidate (an upper bound of tau + 2 emax)
     double ub = 0.0;
     float sure = -__builtin_inff();   // lists below it are in the set (ordered = 0)
+    float nearest = 0.f;
     if (!every) {   // every distance is finite
         float lo = __builtin_inff(), hi = -__builtin_inff();
 #pragma unroll
@@ -954,6 +958,7 @@ __global__ __launch_bounds__(256) void k_coarse_select_v(
             hi = fmaxf(hi, __shfl_xor(hi, o));
         }
         float tau = hi, first = lo;
+        nearest = lo;
         int below = 0;   // lists under lo, all among the candidates
         for (int round = 0; round < 3 && lo < hi; round++) {
             const float range = hi - lo, scale = range > 0x1p-100f ? (SV_BINS - 1) / range : 0.f;
@@ -1049,12 +1054,23 @@ __global__ __launch_bounds__(256) void k_coarse_select_v(
         }
     };
     uint64_t cand = 0;   // bit i: list 64 i + lane passes the coarse test ("not above": a NaN keeps the list)
-    int ns = 0;          // lists certainly in the set, fewer than m
+    // lists certainly in the set, fewer than m: a nearest one first, the others behind it
+    int ns = nearest < sure ? 1 : 0;
+    bool near = ns == 0;   // the first place is taken (or there is none)
 #pragma unroll
     for (int i = 0; i < NK; i++) {
         const bool in = key[i] < sure;
-        const uint64_t im = ballot(in);
-        if (in) orow[ns + (int)__builtin_popcountll(im & lanemask_lt())] = 64 * i + lane;
+        uint64_t im = ballot(in);
+        const uint64_t nm = ballot(in && key[i] == nearest);
+        int at = 0;
+        bool rest = in;
+        if (!near && nm) {
+            near = true;
+            rest = in && lane != (int)__builtin_ctzll(nm);
+            im &= ~(1ull << __builtin_ctzll(nm));
+        }
+        if (rest) at = ns + (int)__builtin_popcountll(im & lanemask_lt());
+        if (in) orow[at] = 64 * i + lane;
         ns += (int)__builtin_popcountll(im);
         cand |= (uint64_t)(64 * i + lane < nlist && !in && !(key[i] > lim) ? 1 : 0) << i;
     }

@@ -34,8 +34,8 @@ __device__ __forceinline__ bool in_class(const KClass &c, int qi) {
 
 // List of pair p, or -1 when it probes nothing or its query is outside the pass.
 __device__ __forceinline__ int pair_list(const int32_t *probes, int p, const KClass &c) {
-    const int l = probes[p];
-    return (l >= 0 && in_class(c, p / c.np_stride)) ? l : -1;
+    const int l = probes[p], qi = p / c.np_stride, j = p - qi * c.np_stride;
+    return (l >= 0 && j >= c.plo && j < c.phi && in_class(c, qi)) ? l : -1;
 }
 
 __global__ __launch_bounds__(256) void k_inv_count(Dev S, int npairs, const int32_t *__restrict__ probes,
@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256) void k_merge(Dev S, int nq, int np_stride, con
                                                const uint64_t *__restrict__ partials, int kcap, int out_stride,
                                                int k, int kmul, const int32_t *__restrict__ kpq,
                                                float *__restrict__ dist, int64_t *__restrict__ labels, KClass cls,
-                                               const uint32_t *__restrict__ gthr,
+                                               uint32_t *__restrict__ gthr,
                                                const uint64_t *__restrict__ prior, int prior_stride,
                                                uint64_t *__restrict__ keys_out) {
     __shared__ uint64_t sbuf[4][MG_BUF];
@@ -588,8 +588,9 @@ __global__ __launch_bounds__(256) void k_merge(Dev S, int nq, int np_stride, con
         for (int p0 = 0; p0 < np_stride; p0 += 64) {
             const int p = p0 + lane;
             const int l = p < np_stride ? prow[p] : -1;
-            const int nc = l >= 0 ? list_chunks(S.l_snap[l], sh) : 0;
-            const int64_t slot = nc > 0 ? (int64_t)S.l_pbase[l] + (int64_t)rrow[p] * nc : 0;
+            const int rank = l >= 0 ? rrow[p] : -1;   // -1: a pair of another phase
+            const int nc = rank >= 0 ? list_chunks(S.l_snap[l], sh) : 0;
+            const int64_t slot = nc > 0 ? (int64_t)S.l_pbase[l] + (int64_t)rank * nc : 0;
             const int incl = wave_incl_scan_dpp(nc);
             const int total = readlane_i(incl, 63), excl = incl - nc;
             for (int s0 = 0; s0 < total; s0 += 64) {
@@ -650,6 +651,10 @@ __global__ __launch_bounds__(256) void k_merge(Dev S, int nq, int np_stride, con
             }
         }
     }
+    if (keys_out && gthr && kq > 0) {   // the merged k-th key bounds what the next phase can add
+        const uint64_t kth = (WIDE && kq > 64) ? readlane_u64(res2, kq - 65) : readlane_u64(res, kq - 1);
+        if (lane == 0 && kth != ~0ull) gthr[qi] = (uint32_t)(kth >> 32);
+    }
     for (int h = 0; h < 2; h++) {
         const int r = lane + 64 * h;
         if (r < out_stride) {
@@ -687,14 +692,16 @@ int default_tile(int storage, int d, int C, int kcap) {
 // 388; 500 (16 per list) -, 435, 413; 1,000 (31 per list) -, 699, 520.  On
 // 200k x 128 with 6 pairs per list 57, 62, 141.  For the pass of queries with k > 64
 // the matrix-core scan has to insert up to 128 keys per query and work item
-// one at a time, and pays off later (skewed 5M x 128, a third of the queries
-// at k = 100: 187 pairs per list 3.4 against 6.2 ms, 2,000 per list 28 against
+// one at a time, and pays off later (1M x 128 at k = 100, 1,024 lists, 4 and 16 per
+// tile: 98 pairs per list 0.58 to 1.17 times as fast by data, 195 and up 1.1 to 2.4
+// times for 8 of 9, 0.92 for one; mixed batches, where a third has k = 100 and all
+// are counted, by half their pairs: 187 per list 3.4 against 6.2 ms, 2,000 28 against
 // 20 ms).  Wide rows (no matrix-core scan) take 4 rather than 8: 267 against
 // 374 us at 31 pairs per list of 960 values, 776 against 970 at 125.
 int auto_tile(const Dev &S, int64_t npairs, bool deep) {
     if (S.storage != 0) return 16;
     if (npairs <= 6ll * S.nlist) return 2;
-    if (S.tile != 16 || npairs <= (deep ? 400ll : 16ll) * S.nlist) return 4;
+    if (S.tile != 16 || npairs <= (deep ? 200ll : 16ll) * S.nlist) return 4;
     return 16;
 }
 
@@ -784,9 +791,10 @@ static void launch_scan_t(hipStream_t st, const Dev &S, const SearchBufs &W, con
 }
 
 void launch_search_plan(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const KClass &cls, int snap,
-                        int32_t *heat) {
+                        int32_t *heat, int keep_thr) {
     const int np_stride = cls.np_stride;
     const int npairs = nq * np_stride;
+    if (keep_thr) nq = 0;   // the kernels below only fill the queries' thresholds with it
     const int T = search_tile(S);
     const int64_t lim = item_limit(S, W, npairs);
     const int xcd_cap = (int)((lim + 7) / 8);
@@ -842,7 +850,7 @@ void launch_search_merge(hipStream_t st, const Dev &S, const SearchBufs &W, int 
                          int64_t *labels, const uint64_t *prior, int prior_stride, uint64_t *keys_out) {
     const int np_stride = cls.np_stride;
     // the MFMA scans publish each query's best k-th key; the VALU scan does not
-    const uint32_t *gthr = search_tile(S) == 16 ? W.gthr : nullptr;
+    uint32_t *gthr = search_tile(S) == 16 ? W.gthr : nullptr;
     // results per query beyond 64 need two keys per lane; four waves per query while 4 nq waves fit the chip
 #define SIVF_MERGE(W_, Q_)                                                                                   \
     hipLaunchKernelGGL((k_merge<W_, Q_>), dim3((nq * Q_ + 3) / 4), dim3(256), 0, st, S, nq, np_stride, W.probes,  \

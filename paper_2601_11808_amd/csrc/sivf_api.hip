@@ -29,6 +29,8 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 constexpr int64_t FILL_ROOM = 8192;   // chunks beyond one per (query, probe) pair
 
+constexpr int64_t NEAR_QUERIES = 8000;   // queries from which a search scans nearest lists first
+
 constexpr int NLISTS = 17;   // per-list scratch arrays
 
 int kcap_for(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : (k <= 64 ? 64 : 128)); }
@@ -40,7 +42,7 @@ struct Layout {
     size_t cent, cent_h, cn2, cnorm, cmax, data, sids, sowner, sord, free_slabs, free_pages, pages, dir, len, att, mark,
         ctl, lists, b_assign, b_rank, b_rec, b_seg, b_inv, dt, probes, pair_rank, list_pairs, item_list, item_tile,
         item_chunk, partials, hdata, xnorm, rr_dist, rr_lab, gthr, dt_s, srv_q, srv_k, srv_np, srv_dist, srv_lab,
-        srv_seg, bits;
+        srv_seg, bits, near;
 };
 
 bool config_ok(const sivf_config *c) {
@@ -125,6 +127,7 @@ Layout make_layout(const sivf_config *c) {
     L.xnorm = take((reduced && c->metric == SIVF_L2) || !reduced ? (size_t)ns * C * 4 : 0);
     L.rr_dist = take(reduced ? (size_t)c->max_queries * L.kcap * 4 : 0);
     L.rr_lab = take(reduced ? (size_t)c->max_queries * L.kcap * 8 : 0);
+    L.near = take(reduced ? 0 : (size_t)c->max_queries * L.kcap * 8);   // first results of a search in two phases
     L.gthr = take((size_t)c->max_queries * 4);   // per-query shared thresholds of the MFMA scans
     // serving: one coalesced search batch (query rows, per-row k and nprobe,
     // results at stride max_k, one segment per request)
@@ -303,6 +306,21 @@ sivf_status do_remove(sivf_index *ix, int64_t n, const int64_t *ids, int64_t *n_
     return launched(ix);
 }
 
+// Whether a certified search scans every query's nearest list before the others.
+// Lists are scanned in list order, not in the order of a query's probes, so a scan
+// meets most of them with a loose threshold; after the nearest list it is close to
+// final and few other pairs pass the filter.  Costs a second plan and merge, and the
+// first scan has to fill the chip by itself.  Two phases against one, in ms on 1M x
+// 128 at k = 10: 2,500 queries x 16 of 512 lists 0.80 and 0.73, 5,000 x 16 of 2,048
+// 0.72 and 0.66, 5,000 x 64 1.10 and 1.08, 10,000 x 4 of 512 0.98 and 1.10, 10,000 x 20
+// of 1,024 1.38 and 1.54 (k = 40: 1.78 and 2.32; x 64 at k = 100: 4.3 and 5.8), 10,000 x 64
+// of 4,096 1.68 and 1.72; 5,000 x 64 of 1,024 at k = 100 3.1 and 3.8; 10,000 x 32 of 8,192 (tiles of one query) 1.70 and 1.66.
+// Batches with their own k or nprobe per query stay in one phase (they make a pass per
+// list width already, and a short probe list is mostly its nearest list): 3.20 and 3.06.
+bool near_first(const Dev &S, int64_t nq, int stride, bool deep) {
+    return S.tile == 16 && stride >= 4 && nq >= (deep ? NEAR_QUERIES / 2 : NEAR_QUERIES) && nq >= 2ll * S.nlist;
+}
+
 sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, const int32_t *kpq, int32_t nprobe,
                       const int32_t *npq, float *dist, int64_t *labels, hipStream_t st,
                       hipEvent_t snapshot_taken = nullptr) {
@@ -341,8 +359,8 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     }
     // fp32: partial lists as wide as the call's k needs.  On the certified
     // scan, queries with k > 64 form a pass of their own on the deep schedule
-    // (its lists of 128 keys cost the certified scan more than the VALU scan
-    // pays); the k <= 64 queries keep the certified scan with 64-key lists.
+    // (lists of 128 keys cost every query of a pass); the k <= 64 queries keep
+    // 64-key lists.
     const int kw = kcap_for(k);
     // without a schedule of the caller's own, the tiles follow the batch
     Dev Sm = ix->S, Sd = ix->S;
@@ -353,7 +371,7 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     if (Sm.auto_tile) Sm.tile = auto_tile(Sm, nq * stride, false);
     const bool split = Sm.tile == 16 && kw > 64;
     if (split && Sd.auto_tile) {
-        Sd.tile = auto_tile(Sd, nq * stride, true);
+        Sd.tile = auto_tile(Sd, nq * stride / (kpq ? 2 : 1), true);   // a mixed batch has other queries too
         Sd.persistent = 0;   // one wave per item: 19.2 against 20.4 ms (resident waves) for 10,700 queries at k = 100
     }
     struct Pass {
@@ -387,15 +405,31 @@ sivf_status do_search(sivf_index *ix, int64_t nq, const float *q, int32_t k, con
     }
     for (int i = 0; i < np; i++) {
         const Pass &P = passes[i];
-        launch_search_plan(st, *P.S, ix->W, (int)nq, P.cls, i == 0 ? 1 : 0, i == 0 ? ix->tier.heat : nullptr);
-        if (i == 0 && snapshot_taken && !dev_ok(hipEventRecord(snapshot_taken, st))) return SIVF_ERR_DEVICE;
         const int sk = (split && P.S == &Sd) ? SIVF_PROF_SCAN_DEEP : SIVF_PROF_SCAN;
-        const int pk = prof_begin(ix, sk, st);
-        launch_search_scan(st, *P.S, ix->W, (int)nq, q, stride, P.kw, k, kpq);
-        prof_end(ix, sk, pk, st);
-        const int pm = prof_begin(ix, SIVF_PROF_MERGE, st, i > 0);
-        launch_search_merge(st, *P.S, ix->W, (int)nq, P.cls, P.kw, k, k, 1, kpq, dist, labels, prior, kw);
-        prof_end(ix, SIVF_PROF_MERGE, pm, st);
+        const int phases = !kpq && !npq && near_first(*P.S, nq, stride, P.kw > 64) ? 2 : 1;
+        const uint64_t *pr = prior;
+        int pr_stride = kw;
+        for (int ph = 0; ph < phases; ph++) {
+            KClass cls = P.cls;
+            if (phases == 2) (ph == 0 ? cls.phi : cls.plo) = 1;
+            launch_search_plan(st, *P.S, ix->W, (int)nq, cls, i == 0 && ph == 0 ? 1 : 0, i == 0 ? ix->tier.heat : nullptr,
+                               ph);
+            if (i == 0 && ph == 0 && snapshot_taken && !dev_ok(hipEventRecord(snapshot_taken, st)))
+                return SIVF_ERR_DEVICE;
+            const int pk = prof_begin(ix, sk, st, ph > 0);
+            launch_search_scan(st, *P.S, ix->W, (int)nq, q, stride, P.kw, k, kpq);
+            prof_end(ix, sk, pk, st);
+            const int pm = prof_begin(ix, SIVF_PROF_MERGE, st, i > 0 || ph > 0);
+            if (ph + 1 < phases) {
+                launch_search_merge(st, *P.S, ix->W, (int)nq, P.cls, P.kw, P.kw, k, 1, kpq, nullptr, nullptr, pr, pr_stride,
+                                    ix->W.near);
+                pr = ix->W.near;
+                pr_stride = P.kw;
+            } else {
+                launch_search_merge(st, *P.S, ix->W, (int)nq, P.cls, P.kw, k, k, 1, kpq, dist, labels, pr, pr_stride);
+            }
+            prof_end(ix, SIVF_PROF_MERGE, pm, st);
+        }
     }
     prof_end(ix, SIVF_PROF_SEARCH, ps, st);
     return launched(ix);
@@ -442,6 +476,7 @@ sivf_status sivf_create(const sivf_config *cfg, const float *centroids, void *wo
     S.xnorm = (cfg->storage == SIVF_F32 || cfg->metric == SIVF_L2) ? (float *)(w + L.xnorm) : nullptr;
     ix->W.rr_dist = cfg->storage != SIVF_F32 ? (float *)(w + L.rr_dist) : nullptr;
     ix->W.rr_lab = cfg->storage != SIVF_F32 ? (int64_t *)(w + L.rr_lab) : nullptr;
+    ix->W.near = (uint64_t *)(w + L.near);
     ix->W.gthr = (uint32_t *)(w + L.gthr);
     S.num_slabs = cfg->num_slabs;
     S.num_pages = L.num_pages;

@@ -76,6 +76,7 @@ struct SearchBufs {
     int64_t item_cap;    // entries of item_list / item_tile / item_chunk
     float *rr_dist;      // reduced precision: approximate candidates per query
     int64_t *rr_lab;
+    uint64_t *near;      // [max_queries][kcap] keys of a two-phase search's first phase
     uint32_t *gthr;      // MFMA scans: per query, the best published k-th (R k-th) key's high word
 };
 // One pass of a search over the queries whose k, clamped to [0, k], lies in
@@ -83,9 +84,12 @@ struct SearchBufs {
 // per-query k straddles 64 on a certified-scan schedule runs two passes (k up
 // to 64 on the certified scan, the rest on the deep schedule) that share the
 // coarse probes and the list-length snapshot.
+// A pass may also be scanned in two phases by probe position (plo <= p < phi):
+// the nearest list of every query first, then the others.
 struct KClass {
     const int32_t *kpq;   // per-query k or null (every query asks for k)
     int k, np_stride, lo, hi;
+    int plo = 0, phi = 0x7FFFFFFF;
 };
 inline KClass kclass_all(int np_stride) { return KClass{nullptr, 0, np_stride, -1, 0x7FFFFFFF}; }
 int search_tile(const Dev &S);
@@ -103,8 +107,9 @@ constexpr int DEFAULT_CHUNK_SHIFT = 14;
 // snap = 1: record every list's length (the scan reads only these entries);
 // snap = 0: keep the lengths an earlier pass of the same search recorded.
 // heat (or NULL): per-list probe counts to add this pass's pairs to
+// keep_thr = 1: keep the thresholds that an earlier phase published
 void launch_search_plan(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const KClass &cls, int snap,
-                        int32_t *heat = nullptr);
+                        int32_t *heat = nullptr, int keep_thr = 0);
 void launch_search_scan(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const float *q, int np_stride,
                         int kcap, int k, const int32_t *k_per_query);
 // its certified matrix-core form (tile 16), per metric
@@ -113,7 +118,8 @@ void launch_scan_cert_l2(hipStream_t st, const Dev &S, const SearchBufs &W, cons
 void launch_scan_cert_ip(hipStream_t st, const Dev &S, const SearchBufs &W, const float *q, int np_stride, int kcap, int k,
                          const int32_t *k_per_query, int npairs);
 // prior (or NULL): per query, prior_stride sorted keys merged in as one more source;
-// keys_out (or NULL): sorted keys (stride out_stride) instead of dist / labels
+// keys_out (or NULL): sorted keys (stride out_stride) instead of dist / labels (and, after an MFMA scan, the
+// query's merged k-th key as its threshold)
 void launch_search_merge(hipStream_t st, const Dev &S, const SearchBufs &W, int nq, const KClass &cls, int kcap,
                          int out_stride, int k, int kmul, const int32_t *k_per_query, float *dist,
                          int64_t *labels, const uint64_t *prior = nullptr, int prior_stride = 0,

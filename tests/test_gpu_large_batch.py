@@ -1,0 +1,54 @@
+"""Searches of thousands of queries on the default schedule, which scan every query's nearest list first and the
+others with its threshold.  Distances and labels equal those of the FP32 scan on a schedule set by hand, bit for bit."""
+import numpy as np
+import pytest
+
+import paper_2601_11808_amd as sivf
+
+pytestmark = pytest.mark.gpu
+
+
+# k up to 64 takes two phases from 8,000 queries and 4 probes on, k above 64 from 4,000; 3 probes and 7,999 and 3,999
+# queries take one.  Lists shorter than k, empty ones, and a query's nearest list among them.
+@pytest.mark.parametrize("metric,d", [(0, 24), (1, 24), (0, 100)])
+def test_nearest_list_first(metric, d):
+    rng = np.random.default_rng([31, metric, d])
+    sizes = [6000, 2500, 700, 65, 64, 63, 9, 1, 0, 0] + list(rng.integers(0, 400, 50))
+    nlist, n = len(sizes), sum(sizes)
+    cent = (rng.standard_normal((nlist, d)) * 3).astype(np.float32)
+    x = (cent[np.repeat(np.arange(nlist), sizes)] + rng.standard_normal((n, d))).astype(np.float32)
+    x[1::53] = x[0::53][:x[1::53].shape[0]]          # equal rows under other ids
+    ix = sivf.Index(d, nlist, cent, metric=metric, slab_capacity=32, num_slabs=n // 32 + 4 * nlist, id_capacity=n,
+                    max_batch=n, max_queries=9000, max_k=128, max_nprobe=nlist)
+    ix.add(x, rng.permutation(n))
+    assert ix.sync() == 0
+    q = (cent[rng.integers(0, nlist, 9000)] + rng.standard_normal((9000, d))).astype(np.float32)
+    cases = [(9000, 10, 4), (8000, 1, 9), (8000, 64, 60), (8007, 33, 20), (7999, 10, 20), (8000, 10, 3), (4000, 65, 60),
+             (4001, 128, 7), (3999, 100, 20)]
+    got = [[t.cpu().numpy() for t in ix.search(q[:nq], k, p)] for nq, k, p in cases]
+    assert ix.sync() == 0
+    ix.set_search_schedule(8, 12, 0)
+    for (nq, k, p), g in zip(cases, got):
+        want = [t.cpu().numpy() for t in ix.search(q[:nq], k, p)]
+        assert ix.sync() == 0
+        assert all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(g, want)), (nq, k, p)
+
+
+def test_nearest_list_first_with_host_tier():
+    """Lists moved to host memory: their results join the first phase's, and the second's."""
+    rng = np.random.default_rng(32)
+    d, nlist, n = 32, 20, 12000
+    cent = (rng.standard_normal((nlist, d)) * 3).astype(np.float32)
+    x = (cent[rng.integers(0, nlist, n)] + rng.standard_normal((n, d))).astype(np.float32)
+    ix = sivf.Index(d, nlist, cent, slab_capacity=32, num_slabs=n // 32 + 4 * nlist, id_capacity=n, max_batch=n,
+                    max_queries=8000, max_k=100, max_nprobe=nlist, delete_mode=sivf.DELETE_LAZY)
+    ix.add(x, np.arange(n))
+    q = (cent[rng.integers(0, nlist, 8000)] + rng.standard_normal((8000, d))).astype(np.float32)
+    want = [[t.cpu().numpy() for t in ix.search(q, k, 8)] for k in (10, 100)]
+    ix.tier_attach(n // 32 + 4 * nlist)
+    ix.tier_offload([0, 3, 4, 11])
+    assert ix.sync() == 0
+    for k, w in zip((10, 100), want):
+        got = [t.cpu().numpy() for t in ix.search(q, k, 8)]
+        assert ix.sync() == 0
+        assert all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(got, w)), k
