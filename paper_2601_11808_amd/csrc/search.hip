@@ -709,13 +709,16 @@ int search_tile(const Dev &S) { return S.tile; }
 
 // Exact FP32 re-rank: one wave per query; lane i recomputes the canonical
 // FP32 distance of candidate i from the fp32 shadow row, then the wave sorts
-// the keys and keeps the query's k best.
+// the keys and keeps the query's k best.  A row's 16-byte chunks lie C slots
+// apart, so a large batch is bound by the lines its gathers touch (16,000 queries x
+// 40 rows of 96 values: 0.3 ms), a small one by the latency of a lane's loads:
+// eight are in flight at once and the query comes through the scalar cache.
 __global__ __launch_bounds__(256) void k_rerank(Dev S, int nq, const float *__restrict__ q, int kc,
                                                 const int64_t *__restrict__ cand, int k, int kmul,
                                                 const int32_t *__restrict__ kpq, float *__restrict__ dist,
                                                 int64_t *__restrict__ labels) {
-    const int w = threadIdx.x >> 6, lane = lane_id();
-    const int qi = blockIdx.x * 4 + w;
+    const int lane = lane_id();
+    const int qi = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (qi >= nq) return;
     const int kq = query_k(kpq, k, qi);
     const int nc = min(kq * kmul, kc);
@@ -725,23 +728,30 @@ __global__ __launch_bounds__(256) void k_rerank(Dev S, int nq, const float *__re
         const int64_t id = cand[(int64_t)qi * kc + lane];
         const uint32_t g = id >= 0 ? S.att[id] : INVALID;
         if (g != INVALID) {
-            const float4 *xp = S.data + (int64_t)(g / C) * S.dp4 * C + g % C;
+            const f32x4_t *xp = reinterpret_cast<const f32x4_t *>(S.data) + (int64_t)(g / C) * S.dp4 * C + g % C;
             const float *qr = q + (int64_t)qi * d;
             float r = 0.f;
-            for (int c = 0; c < S.dp4; c++) {
-                const float4 xv = xp[(int64_t)c * C];
-                const float xs[4] = {xv.x, xv.y, xv.z, xv.w};
-                for (int e = 0; e < 4; e++) {
-                    const int j = 4 * c + e;
-                    if (j < d) {
-                        if (S.metric == 0) {
-                            const float t = qr[j] - xs[e];
-                            r = __builtin_fmaf(t, t, r);
-                        } else {
-                            r = __builtin_fmaf(qr[j], xs[e], r);
-                        }
-                    }
+            auto term = [&](float qv, float xv) {
+                if (S.metric == 0) {
+                    const float t = qv - xv;
+                    r = __builtin_fmaf(t, t, r);
+                } else {
+                    r = __builtin_fmaf(qv, xv, r);
                 }
+            };
+            int c = 0;
+            for (; 4 * c + 32 <= d; c += 8) {
+                f32x4_t x[8];
+#pragma unroll
+                for (int i = 0; i < 8; i++) x[i] = xp[(int64_t)(c + i) * C];
+#pragma unroll
+                for (int i = 0; i < 32; i++) term(qr[4 * c + i], x[i >> 2][i & 3]);
+            }
+            for (; c < S.dp4; c++) {
+                const f32x4_t x = xp[(int64_t)c * C];
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (4 * c + i < d) term(qr[4 * c + i], x[i]);
             }
             key = make_key(r, (uint32_t)id, S.metric);
         }
