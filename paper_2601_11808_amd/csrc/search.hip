@@ -384,10 +384,19 @@ __global__ __launch_bounds__(1024) void k_inv_small(Dev S, int T, int sh0, int64
 // Distances of 64 consecutive list positions (lane <-> slot) to the T queries
 // of a tile, in the canonical order (dimensions ascending, one fma each), then
 // offered to each query's top-k.  QV(t, c) gives query t's dimension chunk c.
+// Where there are more items than the chip runs at once, lane t (t < nt, query qg)
+// reads the best k-th key that finished items have published for its query, and
+// publishes this item's at its end: a candidate behind it cannot be a result, so an
+// item scanned late sorts few keys of its own and the merge reads fewer (1,000 queries
+// x 16 of 1,024 lists, 500k x 128: the step 544 -> 527 us).  Read at every 64 rows it
+// costs more than it saves (200 us instead of 60 for 100 queries x 16), and so it does
+// where all items run at once (37 queries x 16: 60 -> 63 us).
 #define SIVF_SCAN_RANGE(QV)                                                                      \
     const int cs_ = __builtin_ctz(C), cm_ = C - 1; /* slab capacities are powers of two */       \
     const int nslab = (len + cm_) >> cs_;                                                        \
     int wbase = -(1 << 30), wslab = 0; /* lane j holds the slab of ordinal wbase + j */          \
+    const bool share_ = S.ctl[CTL_XB + 8] > 2 * FILL_ITEMS;                                      \
+    const uint32_t pub = share_ && lane < nt ? __hip_atomic_load(gthr + qg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0u; \
     for (int base = p0; base < p1; base += 64) {                                                 \
         const int p = base + lane;                                                               \
         const bool valid = p < p1;                                                               \
@@ -428,6 +437,7 @@ __global__ __launch_bounds__(1024) void k_inv_small(Dev S, int T, int sh0, int64
         }                                                                                        \
         const uint32_t id = S.sids[(int64_t)slab * C + slot];                                    \
         _Pragma("unroll") for (int t = 0; t < T; t++) {                                          \
+            K.thr[t] = min(K.thr[t], (uint32_t)__builtin_amdgcn_readlane(pub, t));               \
             if (t < nt) topk_offer(K, t, live_, key_hi<METRIC>(acc[t]), id, buf, skq, kcap);     \
         }                                                                                        \
     }                                                                                            \
@@ -439,7 +449,11 @@ __global__ __launch_bounds__(1024) void k_inv_small(Dev S, int T, int sh0, int64
             if (lane < kcap) dst[lane] = K.top[t];                                               \
             if (WIDE && lane + 64 < kcap) dst[64 + lane] = K.top2[WIDE ? t : 0];                 \
         }                                                                                        \
-    }
+    }                                                                                            \
+    uint32_t mine = ~0u;                                                                         \
+    _Pragma("unroll") for (int t = 0; t < T; t++) mine = lane == t ? K.thr[t] : mine;            \
+    if (share_ && lane < nt && mine < pub && skq[lane & (T - 1)] > 0)                                                   \
+        __hip_atomic_fetch_min(gthr + qg, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
 
 // Dimension chunks in flight per lane.  The fewer queries share a chunk, the
@@ -458,7 +472,8 @@ __global__ __launch_bounds__(64) void k_scan_sq(Dev S, const int32_t *__restrict
                                                 const int32_t *__restrict__ item_chunk,
                                                 const int32_t *__restrict__ list_pairs,
                                                 const float *__restrict__ q, int np_stride, int kcap, int k,
-                                                const int32_t *__restrict__ kpq, uint64_t *__restrict__ partials) {
+                                                const int32_t *__restrict__ kpq, uint64_t *__restrict__ partials,
+                                                uint32_t *__restrict__ gthr) {
     __shared__ uint64_t buf[T * 64];
     __shared__ int skq[T];
     const int lane = threadIdx.x;
@@ -474,7 +489,8 @@ __global__ __launch_bounds__(64) void k_scan_sq(Dev S, const int32_t *__restrict
         qrow[t] = reinterpret_cast<const float4 *>(q + (int64_t)(pr / np_stride) * S.d);
     }
     __syncthreads();
-    if (lane < T) skq[lane] = lane < nt ? query_k(kpq, k, pairs[lane] / np_stride) : 0;
+    const int qg = pairs[lane < nt ? lane : 0] / np_stride;
+    if (lane < T) skq[lane] = lane < nt ? query_k(kpq, k, qg) : 0;
     __syncthreads();
     topk_init(K, skq);
 #define SIVF_QV_SQ(t, c) qrow[t][c]
@@ -490,7 +506,7 @@ __global__ __launch_bounds__(64) void k_scan(Dev S, const int32_t *__restrict__ 
                                              const int32_t *__restrict__ item_chunk,
                                              const int32_t *__restrict__ list_pairs, const float *__restrict__ q,
                                              int np_stride, int kcap, int k, const int32_t *__restrict__ kpq,
-                                             uint64_t *__restrict__ partials) {
+                                             uint64_t *__restrict__ partials, uint32_t *__restrict__ gthr) {
     extern __shared__ float4 sq[];   // [T][dp4]
     __shared__ uint64_t buf[T * 64];
     __shared__ int skq[T];
@@ -516,7 +532,8 @@ __global__ __launch_bounds__(64) void k_scan(Dev S, const int32_t *__restrict__ 
             sq[t * dp4 + c] = v;
         }
     }
-    if (lane < T) skq[lane] = lane < nt ? query_k(kpq, k, pairs[lane] / np_stride) : 0;
+    const int qg = pairs[lane < nt ? lane : 0] / np_stride;
+    if (lane < T) skq[lane] = lane < nt ? query_k(kpq, k, qg) : 0;
     __syncthreads();
     topk_init(K, skq);
 #define SIVF_QV_LDS(t, c) sq[(t) * dp4 + (c)]
@@ -781,7 +798,7 @@ static void launch_scan_p(hipStream_t st, const Dev &S, const SearchBufs &W, con
     const bool sq = (S.d % 4 == 0) && (((uintptr_t)q & 15) == 0);
 #define SIVF_LAUNCH_SCAN(KERN, SMEM)                                                                         \
     hipLaunchKernelGGL(KERN, dim3(scan_grid(KERN, S, W, npairs, SMEM)), dim3(64), SMEM, st, S, W.item_list,   \
-                       W.item_tile, W.item_chunk, W.list_pairs, q, np_stride, kcap, k, kpq, W.partials)
+                       W.item_tile, W.item_chunk, W.list_pairs, q, np_stride, kcap, k, kpq, W.partials, W.gthr)
     if (sq) {
         if (S.metric == 0) SIVF_LAUNCH_SCAN((k_scan_sq<T, 0, WIDE, PERS>), 0);
         else SIVF_LAUNCH_SCAN((k_scan_sq<T, 1, WIDE, PERS>), 0);
@@ -860,7 +877,7 @@ void launch_search_merge(hipStream_t st, const Dev &S, const SearchBufs &W, int 
                          int64_t *labels, const uint64_t *prior, int prior_stride, uint64_t *keys_out) {
     const int np_stride = cls.np_stride;
     // the MFMA scans publish each query's best k-th key; the VALU scan does not
-    uint32_t *gthr = search_tile(S) == 16 ? W.gthr : nullptr;
+    uint32_t *gthr = W.gthr;
     // results per query beyond 64 need two keys per lane; four waves per query while 4 nq waves fit the chip
 #define SIVF_MERGE(W_, Q_)                                                                                   \
     hipLaunchKernelGGL((k_merge<W_, Q_>), dim3((nq * Q_ + 3) / 4), dim3(256), 0, st, S, nq, np_stride, W.probes,  \
