@@ -8,6 +8,7 @@ import pytest
 import oracle
 import paper_2601_11808_amd as sivf
 from tests.gpu_common import compare_results
+from tests.invariants import check_dump, same_membership
 
 pytestmark = pytest.mark.gpu
 
@@ -126,3 +127,34 @@ def test_delete_moves(d, C, storage):
         keep = np.setdiff1d(live, rm)
         if keep.shape[0]:
             np.testing.assert_array_equal(ix.get_rows(keep).cpu().numpy(), x[row_of[keep]])
+
+
+# compaction takes the holes by validity words: slabs shorter than a word, of one, and of two
+@pytest.mark.parametrize("C", [4, 32, 64, 128])
+def test_compaction_slab_words(C):
+    rng = np.random.default_rng([25, C])
+    d, sizes = 20, [1500, 1, 2, 300, 0, 64, 65, 257] + [90] * 20
+    nlist, n = len(sizes), sum(sizes)
+    cent = (rng.standard_normal((nlist, d)) * 8).astype(np.float32)
+    x = (cent[np.repeat(np.arange(nlist), sizes)] + rng.standard_normal((n, d))).astype(np.float32)
+    ids = rng.permutation(n)
+    slabs = n // C + 2 * nlist
+    ix = sivf.Index(d, nlist, cent, slab_capacity=C, num_slabs=slabs, id_capacity=n, max_batch=n, max_queries=64,
+                    max_k=16, max_nprobe=16, delete_mode=sivf.DELETE_LAZY)
+    ref = oracle.OracleIndex(d, nlist, cent, 0, C, slabs, n)
+    ix.add(x, ids)
+    assert ix.sync() == 0 and ref.add(x, ids) == 0
+    q = x[rng.integers(0, n, 64)]
+    live = ids.copy()
+    for share in (0.01, 0.3, 0.6, 1.0):
+        rm = rng.choice(live, max(1, int(share * live.shape[0])), replace=False).astype(np.int64)
+        ix.remove(rm)
+        dead = int(ix.compact(0.0).item())
+        assert ix.sync() == 0 and ref.remove(rm)[0] == 0 and dead == rm.shape[0]
+        live = np.setdiff1d(live, rm)
+        check_dump(ix.dump(), C, slabs, lazy=True)
+        assert same_membership(ix.membership(), ref.membership())
+        gd, gl = ix.search(q, 10, 16)
+        assert ix.sync() == 0
+        st, rd, rl = ref.search(q, 10, 16)
+        assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
