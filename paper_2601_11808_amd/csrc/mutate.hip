@@ -56,42 +56,58 @@ __global__ __launch_bounds__(256) void k_add_prepare(Dev S, int n, const int64_t
 }
 
 // fresh_only: the call may not hold live ids (SIVF_ERR_LIVE_ID otherwise).
-template <bool BLK>
-__global__ __launch_bounds__(256) void k_add_count(Dev S, int n, const int64_t *__restrict__ ids,
-                                                   const int32_t *__restrict__ assign, int32_t *__restrict__ rank,
-                                                   int fresh_only) {
+template <int MODE>
+__global__ __launch_bounds__(AggShape<MODE>::NT) void k_add_count(Dev S, int n, const int64_t *__restrict__ ids,
+                                                                  const int32_t *__restrict__ assign,
+                                                                  int32_t *__restrict__ rank, int fresh_only) {
+    constexpr int NT = AggShape<MODE>::NT, R = AggShape<MODE>::R;
     extern __shared__ int32_t hist[];
     // no early return: this kernel may fail the call while other waves of the
     // block are still starting, and every thread must reach the block's
     // barriers; a failed call's counts are cleared by the admission kernel
     const bool failed = call_failed(S.ctl);
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const bool active = i < n && !failed;
-    const int64_t u = active ? ids[i] : 0;
-    bool win = active && S.mark[u] == i;
-    int l = win ? assign[i] : 0;
-    // a row with no valid list (non-finite input) fails the whole call
-    const bool bad = win && (unsigned)l >= (unsigned)S.nlist;
-    if (ballot(bad) && lane_id() == 0) fail_call(S.ctl, -1);
-    if (bad) {
-        win = false;
-        l = 0;
+    const int i0 = blockIdx.x * (NT * R) + threadIdx.x;
+    int l[R], at[R];
+    bool win[R], live[R];
+    uint32_t g[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = i0 + r * NT;
+        const bool active = i < n && !failed;
+        const int64_t u = active ? ids[i] : 0;
+        win[r] = active && S.mark[u] == i;
+        l[r] = win[r] ? assign[i] : 0;
+        g[r] = win[r] ? S.att[u] : INVALID;
     }
-    const int r = list_agg_inc<BLK>(S.l_acnt, l, win, hist, S.nlist, true);
-    if (active) rank[i] = win ? r : -1;
-    const uint32_t g = win ? S.att[u] : INVALID;
-    const bool live = g != INVALID;
-    // with compacting deletes only (the host tier, whose positions index no
-    // device slab, needs lazy deletes)
-    const int lo = (live && !S.bits) ? S.sowner[g / (uint32_t)S.C] : 0;
-    // an upsert frees a position only with compacting deletes (a lazy delete leaves a dead slot)
-    list_agg_inc<BLK>(S.l_prem, lo, live && !S.bits, hist, S.nlist, false);
-    if (ballot(live) && lane_id() == 0) {
-        if (fresh_only)
-            fail_call(S.ctl, -6);
-        else
-            atomicExch(&S.ctl[CTL_UPSERT], S.ctl[CTL_SEQ]);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        // a row with no valid list (non-finite input) fails the whole call
+        const bool bad = win[r] && (unsigned)l[r] >= (unsigned)S.nlist;
+        if (ballot(bad) && lane_id() == 0) fail_call(S.ctl, -1);
+        if (bad) {
+            win[r] = false;
+            l[r] = 0;
+            g[r] = INVALID;
+        }
     }
+    list_agg_inc<MODE>(S.l_acnt, l, win, at, hist, S.nlist, true);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = i0 + r * NT;
+        if (i < n && !failed) rank[i] = win[r] ? at[r] : -1;
+        live[r] = g[r] != INVALID;
+        if (ballot(live[r]) && lane_id() == 0) {
+            if (fresh_only)
+                fail_call(S.ctl, -6);
+            else
+                atomicExch(&S.ctl[CTL_UPSERT], S.ctl[CTL_SEQ]);
+        }
+        // an upsert frees a position with compacting deletes only (a lazy delete leaves a dead slot, and the
+        // host tier, whose positions index no device slab, needs lazy deletes)
+        live[r] = live[r] && !S.bits;
+        l[r] = live[r] ? S.sowner[g[r] / (uint32_t)S.C] : 0;
+    }
+    list_agg_inc<MODE>(S.l_prem, l, live, at, hist, S.nlist, false);
 }
 
 // One block: does the final state fit in the pool?  Also clears the per-list
@@ -379,23 +395,35 @@ __global__ __launch_bounds__(256) void k_rm_validate(Dev S, int n, const int64_t
     if (u < 0 || u >= S.id_capacity) fail_call(S.ctl, -3);
 }
 
-template <bool BLK>
-__global__ __launch_bounds__(256) void k_rm_mark(Dev S, int n, const int64_t *__restrict__ ids,
-                                                 uint32_t *__restrict__ rec, int mode) {
+template <int MODE>
+__global__ __launch_bounds__(AggShape<MODE>::NT) void k_rm_mark(Dev S, int n, const int64_t *__restrict__ ids,
+                                                                uint32_t *__restrict__ rec, int mode) {
+    constexpr int NT = AggShape<MODE>::NT, R = AggShape<MODE>::R;
     extern __shared__ int32_t hist[];
     if (rm_skip(S, mode)) return;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int64_t u = i < n ? ids[i] : -1;
-    const bool active = u >= 0 && u < S.id_capacity;   // out-of-range ids: rejected before (mode 0) or skipped (mode 2)
-    const uint32_t g = active ? atomicExch(&S.att[u], INVALID) : INVALID;
-    const bool hit = g != INVALID;
-    int l = 0;
-    if (hit) {
-        S.sids[g] = INVALID;   // tombstone: this slot no longer holds a live entry
-        l = S.sowner[g / (uint32_t)S.C];
+    const int i0 = blockIdx.x * (NT * R) + threadIdx.x;
+    int l[R], at[R];
+    bool hit[R];
+    uint32_t g[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = i0 + r * NT;
+        const int64_t u = i < n ? ids[i] : -1;
+        const bool active = u >= 0 && u < S.id_capacity;   // out-of-range ids: rejected before (mode 0) or skipped (mode 2)
+        g[r] = active ? atomicExch(&S.att[u], INVALID) : INVALID;
     }
-    list_agg_inc<BLK>(S.l_m, l, hit, hist, S.nlist, false);
-    if (i < n) rec[i] = g;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = i0 + r * NT;
+        hit[r] = g[r] != INVALID;
+        l[r] = 0;
+        if (hit[r]) {
+            S.sids[g[r]] = INVALID;   // tombstone: this slot no longer holds a live entry
+            l[r] = S.sowner[g[r] / (uint32_t)S.C];
+        }
+        if (i < n) rec[i] = g[r];
+    }
+    list_agg_inc<MODE>(S.l_m, l, hit, at, hist, S.nlist, false);
 }
 
 // One block: segment offsets of each list's survivor slots and new lengths.
@@ -430,30 +458,40 @@ __global__ __launch_bounds__(1024) void k_rm_plan(Dev S, int64_t *n_removed, int
 // hole of list l (in any order) is stored at seg[l_off[l] + h].  The blocks past
 // the first nb map the tail-window entries to their lists for the move: entries
 // l_off[l] .. +l_m[l] belong to list l (one wave per list).
-template <bool BLK>
-__global__ __launch_bounds__(256) void k_rm_holes(Dev S, int n, int nb, const uint32_t *__restrict__ rec,
-                                                  int32_t *__restrict__ seg, int32_t *__restrict__ emap, int mode) {
+template <int MODE>
+__global__ __launch_bounds__(AggShape<MODE>::NT) void k_rm_holes(Dev S, int n, int nb, const uint32_t *__restrict__ rec,
+                                                                 int32_t *__restrict__ seg, int32_t *__restrict__ emap,
+                                                                 int mode) {
+    constexpr int NT = AggShape<MODE>::NT, R = AggShape<MODE>::R;
     extern __shared__ int32_t hist[];
     if (rm_skip(S, mode)) return;
     if ((int)blockIdx.x >= nb) {
-        const int l = ((int)blockIdx.x - nb) * 4 + (threadIdx.x >> 6);
+        const int l = ((int)blockIdx.x - nb) * (NT / 64) + (threadIdx.x >> 6);
         if (l >= S.nlist) return;
         const int m = S.l_m[l], o = S.l_off[l];
         for (int j = lane_id(); j < m; j += 64) emap[o + j] = l;
         return;
     }
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t g = i < n ? rec[i] : INVALID;
-    const bool hit = g != INVALID;
-    int l = 0;
-    bool hole = false;
-    if (hit) {
-        const uint32_t slab = g / (uint32_t)S.C;
-        l = S.sowner[slab];
-        hole = S.sord[slab] * S.C + (int)(g % (uint32_t)S.C) < S.l_newlen[l];
+    const int i0 = blockIdx.x * (NT * R) + threadIdx.x;
+    int l[R], h[R];
+    bool hole[R];
+    uint32_t g[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) g[r] = i0 + r * NT < n ? rec[i0 + r * NT] : INVALID;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        l[r] = 0;
+        hole[r] = false;
+        if (g[r] != INVALID) {
+            const uint32_t slab = g[r] / (uint32_t)S.C;
+            l[r] = S.sowner[slab];
+            hole[r] = S.sord[slab] * S.C + (int)(g[r] % (uint32_t)S.C) < S.l_newlen[l[r]];
+        }
     }
-    const int h = list_agg_inc<BLK>(S.l_h, l, hole, hist, S.nlist, true);
-    if (hole) seg[S.l_off[l] + h] = (int32_t)g;
+    list_agg_inc<MODE>(S.l_h, l, hole, h, hist, S.nlist, true);
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (hole[r]) seg[S.l_off[l[r]] + h[r]] = (int32_t)g[r];
 }
 
 __global__ __launch_bounds__(256) void k_rm_expand(Dev S, int32_t *__restrict__ emap, int mode) {
@@ -618,31 +656,42 @@ __global__ void k_rm_lazy_begin(int32_t *ctl) {
 // removal (Theorem 3).  Nothing moves; the slot stays dead until compaction.
 // An entry in the host tier loses its bit in the device-resident cold bitmap
 // the same way.
-template <bool BLK>
-__global__ __launch_bounds__(256) void k_rm_lazy(Dev S, int n, const int64_t *__restrict__ ids, int mode) {
+template <int MODE>
+__global__ __launch_bounds__(AggShape<MODE>::NT) void k_rm_lazy(Dev S, int n, const int64_t *__restrict__ ids, int mode) {
+    constexpr int NT = AggShape<MODE>::NT, R = AggShape<MODE>::R;
     extern __shared__ int32_t hist[];
     if (rm_skip(S, mode == 1 ? 1 : 0)) return;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int64_t u = i < n ? ids[i] : -1;
-    const bool active = u >= 0 && u < S.id_capacity;
-    const uint32_t g = active ? atomicExch(&S.att[u], INVALID) : INVALID;
-    bool gone = false, cold = false;
-    int l = 0;
-    if (g != INVALID) {
-        cold = (g & COLD_BIT) != 0;
-        const uint32_t pos = g & ~COLD_BIT;
-        const int64_t slab = pos / (uint32_t)S.C;
-        const int slot = (int)(pos % (uint32_t)S.C);
-        const uint64_t bit = 1ull << (slot & 63);
-        const uint64_t old = __hip_atomic_fetch_and((cold ? S.cbits : S.bits) + slab * S.bw + (slot >> 6), ~bit,
-                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        gone = (old & bit) != 0;
-        l = cold ? S.csowner[slab] : S.sowner[slab];
+    const int i0 = blockIdx.x * (NT * R) + threadIdx.x;
+    int l[R], at[R];
+    bool dead[R];
+    uint32_t g[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int64_t u = i0 + r * NT < n ? ids[i0 + r * NT] : -1;
+        const bool active = u >= 0 && u < S.id_capacity;
+        g[r] = active ? atomicExch(&S.att[u], INVALID) : INVALID;
     }
-    list_agg_inc<BLK>(S.l_dead, l, gone && !cold, hist, S.nlist, false);
-    if (gone && cold) atomicAdd(&S.cdead[l], 1);
-    const uint64_t gm = ballot(gone);
-    if (gm && lane_id() == __builtin_ctzll(gm)) atomicAdd(&S.ctl[CTL_RMTOT], (int)__builtin_popcountll(gm));
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        bool gone = false, cold = false;
+        l[r] = 0;
+        if (g[r] != INVALID) {
+            cold = (g[r] & COLD_BIT) != 0;
+            const uint32_t pos = g[r] & ~COLD_BIT;
+            const int64_t slab = pos / (uint32_t)S.C;
+            const int slot = (int)(pos % (uint32_t)S.C);
+            const uint64_t bit = 1ull << (slot & 63);
+            const uint64_t old = __hip_atomic_fetch_and((cold ? S.cbits : S.bits) + slab * S.bw + (slot >> 6), ~bit,
+                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            gone = (old & bit) != 0;
+            l[r] = cold ? S.csowner[slab] : S.sowner[slab];
+        }
+        if (gone && cold) atomicAdd(&S.cdead[l[r]], 1);
+        const uint64_t gm = ballot(gone);
+        if (gm && lane_id() == __builtin_ctzll(gm)) atomicAdd(&S.ctl[CTL_RMTOT], (int)__builtin_popcountll(gm));
+        dead[r] = gone && !cold;
+    }
+    list_agg_inc<MODE>(S.l_dead, l, dead, at, hist, S.nlist, false);
 }
 
 __global__ void k_rm_lazy_end(Dev S, int64_t *n_removed) {
@@ -865,12 +914,16 @@ static unsigned blocks(int64_t threads, int per = 256) { return (unsigned)((thre
 // Per-list LDS histograms when nlist ints fit in 64 KiB.
 static bool blk_hist(const Dev &S) { return S.nlist <= 16384; }
 static size_t hist_bytes(const Dev &S) { return blk_hist(S) ? (size_t)S.nlist * 4 : 0; }
-#define SIVF_LAUNCH_BLK(K, grid, st, S, ...)                                                                  \
+static int agg_mode(const Dev &S, int64_t n) { return !blk_hist(S) ? 0 : n < BATCH_BLOCKS ? 1 : 2; }
+// the launch of K over n entries; `more` blocks follow those of the entries
+static unsigned agg_blocks(const Dev &S, int64_t n) { return blocks(n, agg_mode(S, n) == 2 ? 4096 : 256); }
+#define SIVF_LAUNCH_AGG(K, n, more, st, S, ...)                                                               \
     do {                                                                                                     \
-        if (blk_hist(S))                                                                                     \
-            hipLaunchKernelGGL(K<true>, dim3(grid), dim3(256), hist_bytes(S), st, S, __VA_ARGS__);          \
-        else                                                                                                 \
-            hipLaunchKernelGGL(K<false>, dim3(grid), dim3(256), 0, st, S, __VA_ARGS__);                     \
+        const int am = agg_mode(S, n);                                                                       \
+        const dim3 ag(agg_blocks(S, n) + (more));                                                            \
+        if (am == 2) hipLaunchKernelGGL(K<2>, ag, dim3(1024), hist_bytes(S), st, S, __VA_ARGS__);            \
+        else if (am == 1) hipLaunchKernelGGL(K<1>, ag, dim3(256), hist_bytes(S), st, S, __VA_ARGS__);        \
+        else hipLaunchKernelGGL(K<0>, ag, dim3(256), 0, st, S, __VA_ARGS__);                                 \
     } while (0)
 
 void launch_add_prepare(hipStream_t st, const Dev &S, int n, const int64_t *ids) {
@@ -878,7 +931,7 @@ void launch_add_prepare(hipStream_t st, const Dev &S, int n, const int64_t *ids)
 }
 
 void launch_add_count(hipStream_t st, const Dev &S, int n, const int64_t *ids, const Batch &B, int fresh_only) {
-    SIVF_LAUNCH_BLK(k_add_count, blocks(n), st, S, n, ids, B.assign, B.rank, fresh_only);
+    SIVF_LAUNCH_AGG(k_add_count, n, 0, st, S, n, ids, B.assign, B.rank, fresh_only);
 }
 
 void launch_add_admit(hipStream_t st, const Dev &S) {
@@ -918,9 +971,10 @@ static void launch_move(hipStream_t st, const Dev &S, int n, const Batch &B, int
 
 void launch_remove(hipStream_t st, const Dev &S, int n, const int64_t *ids, int64_t *n_removed, const Batch &B, int mode) {
     if (mode == 0) hipLaunchKernelGGL(k_rm_validate, dim3(blocks(n)), dim3(256), 0, st, S, n, ids);
-    SIVF_LAUNCH_BLK(k_rm_mark, blocks(n), st, S, n, ids, B.rec, mode);
+    SIVF_LAUNCH_AGG(k_rm_mark, n, 0, st, S, n, ids, B.rec, mode);
     hipLaunchKernelGGL(k_rm_plan, dim3(1), dim3(1024), 0, st, S, n_removed, mode);
-    SIVF_LAUNCH_BLK(k_rm_holes, blocks(n) + blocks(S.nlist, 4), st, S, n, (int)blocks(n), B.rec, B.seg, B.inv, mode);
+    SIVF_LAUNCH_AGG(k_rm_holes, n, blocks(S.nlist, agg_mode(S, n) == 2 ? 16 : 4), st, S, n, (int)agg_blocks(S, n), B.rec,
+                    B.seg, B.inv, mode);
     launch_move(st, S, n, B, mode);
     hipLaunchKernelGGL(k_rm_finalize, dim3(blocks(S.nlist)), dim3(256), 0, st, S, mode);
 }
@@ -928,7 +982,7 @@ void launch_remove(hipStream_t st, const Dev &S, int n, const int64_t *ids, int6
 void launch_remove_lazy(hipStream_t st, const Dev &S, int n, const int64_t *ids, int64_t *n_removed, int mode) {
     if (mode == 0) hipLaunchKernelGGL(k_rm_validate, dim3(blocks(n)), dim3(256), 0, st, S, n, ids);
     if (mode != 1) hipLaunchKernelGGL(k_rm_lazy_begin, dim3(1), dim3(64), 0, st, S.ctl);
-    SIVF_LAUNCH_BLK(k_rm_lazy, blocks(n), st, S, n, ids, mode);
+    SIVF_LAUNCH_AGG(k_rm_lazy, n, 0, st, S, n, ids, mode);
     if (mode != 1 && n_removed) hipLaunchKernelGGL(k_rm_lazy_end, dim3(1), dim3(64), 0, st, S, n_removed);
 }
 

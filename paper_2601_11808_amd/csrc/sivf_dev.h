@@ -238,21 +238,29 @@ __device__ __forceinline__ int wave_agg_inc(int32_t *counters, int key, bool act
     return result;
 }
 
-// Block-aggregated form of wave_agg_inc, one key per thread of a block of NT
+// Block-aggregated form of wave_agg_inc, R keys per thread of a block of NT
 // threads: the block counts in an LDS histogram (hist, nkeys entries) first,
 // then each key present reserves its range with one device atomic, so a wave
 // whose lanes hit many different keys does not wait on one returning atomic
-// per key.  Returns each active thread's distinct old value (0 when
+// per key.  rank receives each active key's distinct old value (0 when
 // want_rank is false: the counts are only added).  Every thread of the block
 // must call it.
-template <int NT>
-__device__ __forceinline__ int block_agg_inc(int32_t *counters, int key, bool active, int32_t *hist, int nkeys,
-                                             bool want_rank) {
+template <int NT, int R>
+__device__ __forceinline__ void block_agg_inc(int32_t *counters, const int (&key)[R], const bool (&active)[R],
+                                              int (&rank)[R], int32_t *hist, int nkeys, bool want_rank) {
     const int tid = threadIdx.x;
-    __syncthreads();   // a previous call's readers are done with hist
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < R; r++) any = any || active[r];
+    if (!__syncthreads_or(any)) {   // also: a previous call's readers are done with hist
+#pragma unroll
+        for (int r = 0; r < R; r++) rank[r] = 0;
+        return;
+    }
     for (int k = tid; k < nkeys; k += NT) hist[k] = 0;
     __syncthreads();
-    const int local = active ? atomicAdd(&hist[key], 1) : 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) rank[r] = active[r] ? atomicAdd(&hist[key[r]], 1) : 0;
     __syncthreads();
     for (int k = tid; k < nkeys; k += NT) {
         const int c = hist[k];
@@ -264,16 +272,30 @@ __device__ __forceinline__ int block_agg_inc(int32_t *counters, int key, bool ac
         }
     }
     __syncthreads();
-    return (active && want_rank) ? hist[key] + local : 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) rank[r] = (active[r] && want_rank) ? hist[key[r]] + rank[r] : 0;
 }
 
-// Per-list counters of a mutation kernel: LDS histogram when it fits (BLK),
-// else wave aggregation.
-template <bool BLK>
-__device__ __forceinline__ int list_agg_inc(int32_t *counters, int key, bool active, int32_t *hist, int nkeys,
-                                            bool want_rank) {
-    if (BLK) return block_agg_inc<256>(counters, key, active, hist, nkeys, want_rank);
-    return wave_agg_inc(counters, key, active);
+// Per-list counters of a mutation kernel, by the kernel's mode: 0 wave aggregation
+// (lists whose histogram does not fit in LDS), 1 a histogram per 256 entries, 2 one
+// per 4,096 entries (1,024 threads of 4), for large batches: the atomics on a list's
+// counter are what bounds them, and a block of 256 entries saves few of them on 1,024
+// lists.  250,000 entries: k_add_count 38 -> 11 us, k_rm_mark 29 -> 20, k_rm_holes
+// 40 -> 18; below 65,536 the larger blocks would leave most of the chip idle.
+constexpr int BATCH_BLOCKS = 65536;   // entries from which mode 2 is used
+template <int MODE>
+struct AggShape {
+    static constexpr int NT = MODE == 2 ? 1024 : 256, R = MODE == 2 ? 4 : 1;
+};
+template <int MODE, int R>
+__device__ __forceinline__ void list_agg_inc(int32_t *counters, const int (&key)[R], const bool (&active)[R],
+                                             int (&rank)[R], int32_t *hist, int nkeys, bool want_rank) {
+    if (MODE) {
+        block_agg_inc<AggShape<MODE>::NT>(counters, key, active, rank, hist, nkeys, want_rank);
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; r++) rank[r] = wave_agg_inc(counters, key[r], active[r]);
+    }
 }
 
 // Record the first data-dependent error of a call and stop its later kernels.

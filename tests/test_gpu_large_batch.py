@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import paper_2601_11808_amd as sivf
+from tests.invariants import check_dump
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +53,44 @@ def test_nearest_list_first_with_host_tier():
         got = [t.cpu().numpy() for t in ix.search(q, k, 8)]
         assert ix.sync() == 0
         assert all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(got, w)), k
+
+
+# per-list counts by blocks of 4,096 entries from 65,536 on: either side of the line, a ragged last block, and upserts,
+# repeated and absent ids within such a batch; lazy deletes count through the same blocks
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("n", [65535, 65536, 69633])
+def test_mutation_counts_of_large_batches(n, lazy):
+    rng = np.random.default_rng([33, n])
+    d, nlist, cap = 4, 77, 2 * n
+    cent = (rng.standard_normal((nlist, d)) * 9).astype(np.float32)
+    share = rng.random(nlist) ** 4
+    x = (cent[rng.choice(nlist, n, p=share / share.sum())] + rng.standard_normal((n, d))).astype(np.float32)
+    slabs = 2 * n // 32 + 4 * nlist
+    ix = sivf.Index(d, nlist, cent, slab_capacity=32, num_slabs=slabs, id_capacity=cap, max_batch=n, max_queries=16,
+                    max_k=16, max_nprobe=16, delete_mode=sivf.DELETE_LAZY if lazy else sivf.DELETE_COMPACT)
+    where = {}
+
+    def add(rows, ids):
+        ix.add(rows, ids)
+        assert ix.sync() == 0
+        for i, u in enumerate(ids):
+            where[int(u)] = rows[i]
+
+    def check():
+        got = ix.membership()
+        assert sum(len(v) for v in got.values()) == len(where)
+        check_dump(ix.dump(), 32, slabs, lazy=lazy)
+        live = np.fromiter(where, np.int64)
+        np.testing.assert_array_equal(ix.get_rows(live).cpu().numpy(), np.stack(list(where.values())))
+
+    add(x, rng.permutation(cap)[:n])
+    check()
+    ids = rng.permutation(cap)[:n]
+    ids[5::7] = ids[0::7][:ids[5::7].shape[0]]       # the last of equal ids wins
+    add(x[::-1].copy(), ids)
+    check()
+    gone = rng.permutation(cap)[:n]                  # some of them hold nothing
+    removed = ix.remove(gone)
+    assert ix.sync() == 0
+    assert int(removed.item()) == sum(where.pop(int(u), None) is not None for u in gone)
+    check()
