@@ -43,9 +43,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # FP32 VALU peak with packed FP32 off: 256 CUs x 4 SIMD x 16 lanes x 2 flop
-# (fma) x 2.4 GHz.  Dense MFMA peaks: FP32 157.3 TFLOP/s, BF16/FP16 2.5 PFLOP/s.
+# (fma) x 2.4 GHz.  Dense MFMA peak, BF16 / FP16: 2.5 PFLOP/s.
 ALU_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-MFMA32_PEAK_TFLOPS = 157.3
 MFMA16_PEAK_TFLOPS = 2500.0
 
 
@@ -57,14 +56,15 @@ def fp32_scan_roofline(evals, d, scan_ms, tile, traffic=None):
 
     Bound: a list is read once per work item of `tile` queries, so one
     (query, list entry) evaluation moves (4d + 4) / tile bytes of slab rows and
-    ids; at tile 16 that is 0.75 * 16 = 12 flop/B of exact-distance work
-    against a ridge of 157.3 / 8 = 19.7 flop/B, so the certified scan is
-    HBM-bound and is reported against the HBM peak.  The VALU scan (tiles 4
+    ids; at tile 16 that is 16 flop/B of matrix-core work against a ridge of
+    2500 / 8 = 313 flop/B, so the certified scan is HBM-bound and is reported
+    against the HBM peak.  The VALU scan (tiles 4
     and 8) sits at 3d*tile/(4d+4) <= 6 flop/B, under its own ridge of 9.8 only
     because packed FP32 is off, and is reported against the FP32 VALU peak on
     its 3d flops per evaluation.  The matrix-core accounting of the certified
-    scan (2 * 4 * ceil(d / 4) flops per evaluation against the FP32 MFMA peak)
-    is kept beside it.  Where consecutive tiles of one list re-read its chunk
+    scan (its bf16 filter: rows rounded once, queries in two parts, so 2 * 2 *
+    32 * ceil(d / 32) flops per evaluation against the bf16 MFMA peak) is kept
+    beside it.  Where consecutive tiles of one list re-read its chunk
     from L2 / MALL (many queries on few long lists), the per-tile byte count
     exceeds what HBM can deliver in the measured time: the scan is then
     reported against the matrix-core peak, with the HBM model beside it."""
@@ -72,17 +72,17 @@ def fp32_scan_roofline(evals, d, scan_ms, tile, traffic=None):
     if tile == 16:
         per_eval = (4.0 * d + 4.0) / tile
         gbps = evals * per_eval / (scan_ms * 1e-3) / 1e9
-        tf = evals * 2.0 * 4 * ((d + 3) // 4) / (scan_ms * 1e-3) / 1e12
+        tf = evals * 4.0 * 32 * ((d + 31) // 32) / (scan_ms * 1e-3) / 1e12
         hbm = {"bound": "hbm", "kernel": "k_scan_cert", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
                "unit": "GB/s", "frac": round(gbps / HBM_PEAK_GBPS, 4),
                "bytes_per_eval": per_eval, "algorithmic_bytes_per_launch": int(evals * per_eval)}
-        mf = {"achieved_tflops": round(tf, 3), "peak_tflops": MFMA32_PEAK_TFLOPS,
-              "frac": round(tf / MFMA32_PEAK_TFLOPS, 4), "flops_per_eval": 2 * 4 * ((d + 3) // 4)}
+        mf = {"achieved_tflops": round(tf, 3), "peak_tflops": MFMA16_PEAK_TFLOPS,
+              "frac": round(tf / MFMA16_PEAK_TFLOPS, 4), "flops_per_eval": 4 * 32 * ((d + 31) // 32)}
         if gbps <= HBM_PEAK_GBPS:
             roof = dict(hbm, mfma=mf)
         else:
             roof = {"bound": "mfma", "kernel": "k_scan_cert", "achieved": mf["achieved_tflops"],
-                    "peak": MFMA32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": mf["frac"],
+                    "peak": MFMA16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": mf["frac"],
                     "flops_per_eval": mf["flops_per_eval"],
                     "hbm_model": dict(hbm, note="per-tile chunk reads exceed HBM peak: served from L2/MALL")}
     else:
@@ -132,13 +132,14 @@ def log(*a):
 
 
 def recorded_traffic(name="k_scan_window_1M.md"):
-    """DRAM bytes per scan launch from the committed counter summary, or None
-    when the scan source changed since the counters were taken."""
+    """DRAM bytes per search of the scan from the committed counter summary, or
+    None when the source of its kernel changed since the counters were taken."""
     prof = os.path.join(ROOT, "profiles", name)
-    src = os.path.join(ROOT, "paper_2601_11808_amd", "csrc", "search.hip")
+    src = {"k_scan_cert_window_1M.md": "scan_cert.h", "k_scan_mfma_precision_10M.md": "scan_mfma.hip"}.get(name, "search.hip")
+    src = os.path.join(ROOT, "paper_2601_11808_amd", "csrc", src)
     try:
-        kv = dict(l.split(": ", 1) for l in open(prof).read().splitlines() if l.startswith(("traffic_", "search_hip")))
-        if hashlib.sha256(open(src, "rb").read()).hexdigest() != kv["search_hip_sha256"].strip():
+        kv = dict(l.split(": ", 1) for l in open(prof).read().splitlines() if l.startswith(("traffic_", "source_")))
+        if hashlib.sha256(open(src, "rb").read()).hexdigest() != kv["source_sha256"].strip():
             return None
         return int(kv["traffic_bytes_per_launch"])
     except (OSError, KeyError, ValueError):

@@ -94,3 +94,45 @@ def test_mutation_counts_of_large_batches(n, lazy):
     assert ix.sync() == 0
     assert int(removed.item()) == sum(where.pop(int(u), None) is not None for u in gone)
     check()
+
+
+def test_nearest_list_first_in_a_graph():
+    """A captured step of a two-phase search and a delete counted by large blocks: every replay equals the eager
+    step on a second index."""
+    import torch
+
+    rng = np.random.default_rng(34)
+    d, nlist, b, nq = 16, 40, 65536, 8000
+    cent = (rng.standard_normal((nlist, d)) * 4).astype(np.float32)
+    ring = (cent[rng.integers(0, nlist, 4 * b)] + rng.standard_normal((4 * b, d))).astype(np.float32)
+
+    def index():
+        ix = sivf.Index(d, nlist, cent, slab_capacity=64, num_slabs=4 * b // 64 + 4 * nlist, id_capacity=4 * b, max_batch=b,
+                        max_queries=nq, max_k=32, max_nprobe=8)
+        ix.add(ring[:b], np.arange(b))
+        assert ix.sync() == 0
+        return ix
+
+    eager, ix = index(), index()
+    dev = dict(device="cuda:0")
+    x, q = torch.zeros(b, d, **dev), torch.zeros(nq, d, **dev)
+    ids, rm = torch.zeros(b, dtype=torch.int64, **dev), torch.zeros(b, dtype=torch.int64, **dev)
+    dist, lab = torch.empty(nq, 20, **dev), torch.empty(nq, 20, dtype=torch.int64, **dev)
+    nrem = torch.zeros(1, dtype=torch.int64, **dev)
+    g = ix.step_graph(x, ids, q, 20, 8, rm, dist, lab, nrem)
+    for t in range(1, 4):
+        new = np.arange(t * b, (t + 1) * b)
+        qt = (cent[rng.integers(0, nlist, nq)] + rng.standard_normal((nq, d))).astype(np.float32)
+        x.copy_(torch.from_numpy(ring[new]))
+        ids.copy_(torch.from_numpy(new))
+        rm.copy_(torch.from_numpy(new - b))
+        q.copy_(torch.from_numpy(qt))
+        g.launch()
+        assert ix.sync() == 0
+        wd, wl, wn = eager.step(ring[new], new, qt, 20, 8, new - b)
+        assert eager.sync() == 0
+        assert torch.equal(dist.view(torch.int32), wd.view(torch.int32)) and torch.equal(lab, wl)
+        assert int(nrem.item()) == int(wn.item()) == b
+        ix.search(qt[:5], 3, 2)                      # eager work between the replays
+        assert {l: sorted(v) for l, v in ix.membership().items()} == {l: sorted(v) for l, v in eager.membership().items()}
+    g.close()
