@@ -218,8 +218,8 @@ __global__ __launch_bounds__(256) void k_add_inv(Dev S, int n, const int32_t *__
 
 // One lane per new entry, in entry order: consecutive lanes fill consecutive
 // slots of a list, so each 16-byte dimension chunk of 64 entries is one
-// contiguous KiB write; the lane reads its source row in order.
-template <bool VEC>
+// contiguous KiB write; the lane reads its source row in order.  For rows whose
+// length or address does not allow 16-byte reads.
 __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restrict__ x,
                                                      const int64_t *__restrict__ ids,
                                                      const int32_t *__restrict__ assign,
@@ -238,15 +238,11 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
     float n32 = 0.f;   // fp32 squared norm (fp32 storage)
     for (int c = 0; c < S.dp4; c++) {
         float4 v;
-        if (VEC) {
-            v = reinterpret_cast<const float4 *>(xr)[c];
-        } else {
-            const int j = 4 * c;
-            v.x = j < S.d ? xr[j] : 0.f;
-            v.y = j + 1 < S.d ? xr[j + 1] : 0.f;
-            v.z = j + 2 < S.d ? xr[j + 2] : 0.f;
-            v.w = j + 3 < S.d ? xr[j + 3] : 0.f;
-        }
+        const int j = 4 * c;
+        v.x = j < S.d ? xr[j] : 0.f;
+        v.y = j + 1 < S.d ? xr[j + 1] : 0.f;
+        v.z = j + 2 < S.d ? xr[j + 2] : 0.f;
+        v.w = j + 3 < S.d ? xr[j + 3] : 0.f;
         dst[(int64_t)c * S.C] = v;
         n32 = fmaf(v.x, v.x, n32);
         n32 = fmaf(v.y, v.y, n32);
@@ -283,14 +279,15 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
     if (S.bits) publish_slot(S, slab, slot);
 }
 
-// LDS-staged form of the scatter (rows of at most 64 chunks, 16-byte aligned):
+// LDS-staged form of the scatter (16-byte aligned rows of whole chunks):
 // one wave per SENT consecutive new entries.  The wave first reads the
 // entries' source rows whole (consecutive lanes read consecutive chunks of a
 // row) into LDS, then writes chunk c of every entry (consecutive lanes,
 // consecutive slots), so reads and writes are both contiguous runs.  16
 // entries per wave keep the staging area at 8.25 KiB (d = 128), so that many
-// waves per CU have loads in flight.
-constexpr int SENT = 16;
+// waves per CU have loads in flight.  Rows of more than SCH chunks go through in pieces
+// of SCH: one lane per row left 5,000 rows of 960 values on 20 blocks (58 us).
+constexpr int SENT = 16, SCH = 64;
 
 __global__ __launch_bounds__(64) void k_add_scatter_lds(Dev S, const float *__restrict__ x,
                                                          const int64_t *__restrict__ ids,
@@ -303,7 +300,7 @@ __global__ __launch_bounds__(64) void k_add_scatter_lds(Dev S, const float *__re
     const int nent = S.ctl[CTL_EBASE];
     if (e0 >= nent) return;
     const int cnt = min(SENT, nent - e0);
-    const int dp4 = S.dp4, ld = dp4 + 1;
+    const int dp4 = S.dp4, ld = min(dp4, SCH) + 1;
     // entry lane (lane < cnt): source row, destination slab and slot
     int i = 0, slab = 0, slot = 0;
     if (lane < cnt) {
@@ -312,61 +309,65 @@ __global__ __launch_bounds__(64) void k_add_scatter_lds(Dev S, const float *__re
         slab = (int)(g / (uint32_t)S.C);
         slot = (int)(g % (uint32_t)S.C);
     }
-    // rows into LDS: 8 chunks per lane in flight (all of a 128-dim batch)
-    const int tot = cnt * dp4;
-    for (int f0 = 0; f0 < tot; f0 += 8 * WAVE) {
-        float4 v[8];
+    float norm = 0.f;   // squared fp32 norm of the stored row, sequential over ascending dimensions
+    for (int c0 = 0; c0 < dp4; c0 += SCH) {
+        const int pc = min(SCH, dp4 - c0);   // chunks of this piece
+        // rows into LDS: 8 chunks per lane in flight (all of a 128-dim batch)
+        const int tot = cnt * pc;
+        for (int f0 = 0; f0 < tot; f0 += 8 * WAVE) {
+            float4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) {
-            const int f = min(f0 + u * WAVE + lane, tot - 1);   // past the end: re-read the last chunk
-            const int r = f / dp4;
-            const int src = __shfl(i, r);
-            v[u] = reinterpret_cast<const float4 *>(x + (int64_t)src * S.d)[f - r * dp4];
-        }
+            for (int u = 0; u < 8; u++) {
+                const int f = min(f0 + u * WAVE + lane, tot - 1);   // past the end: re-read the last chunk
+                const int r = f / pc;
+                const int src = __shfl(i, r);
+                v[u] = reinterpret_cast<const float4 *>(x + (int64_t)src * S.d)[c0 + f - r * pc];
+            }
 #pragma unroll
-        for (int u = 0; u < 8; u++) {
-            const int f = f0 + u * WAVE + lane;
-            const int r = f / dp4;
-            if (f < tot) srow[r * ld + (f - r * dp4)] = v[u];
+            for (int u = 0; u < 8; u++) {
+                const int f = f0 + u * WAVE + lane;
+                const int r = f / pc;
+                if (f < tot) srow[r * ld + (f - r * pc)] = v[u];
+            }
         }
-    }
-    __syncthreads();
-    // chunk c of entry e: lanes e + SENT * h take chunks h, h + WAVE / SENT, ...
-    {
-        const int e = lane % SENT, h = lane / SENT;
-        const int sl = __shfl(slab, e), so = __shfl(slot, e);
-        if (e < cnt) {
-            float4 *dst = S.data + (int64_t)sl * dp4 * S.C + so;
-            for (int c = h; c < dp4; c += WAVE / SENT) dst[(int64_t)c * S.C] = srow[e * ld + c];
+        __syncthreads();
+        // chunk c of entry e: lanes e + SENT * h take chunks h, h + WAVE / SENT, ...
+        {
+            const int e = lane % SENT, h = lane / SENT;
+            const int sl = __shfl(slab, e), so = __shfl(slot, e);
+            if (e < cnt) {
+                float4 *dst = S.data + ((int64_t)sl * dp4 + c0) * S.C + so;
+                for (int c = h; c < pc; c += WAVE / SENT) dst[(int64_t)c * S.C] = srow[e * ld + c];
+            }
         }
+        if (lane < cnt) {
+            const float *row = reinterpret_cast<const float *>(srow + lane * ld);
+            if (S.storage == 0) {
+                for (int j = 0; j < 4 * pc; j++) norm = fmaf(row[j], row[j], norm);
+            } else {
+                // reduced-precision copy (round to nearest even), 8 dims per chunk,
+                // and the fp32 squared norm of the rounded row (L2 scan epilogue)
+                uint4 *hdst = S.hdata + (int64_t)slab * S.dp8 * S.C + slot;
+                for (int c = c0 / 2; c < min(S.dp8, (c0 + SCH) / 2); c++) {
+                    uint32_t hb[8];
+#pragma unroll
+                    for (int q = 0; q < 8; q++) {
+                        const int j = 8 * c + q;
+                        const float v = j < S.d ? row[j - 4 * c0] : 0.f;
+                        hb[q] = S.storage == 1 ? to_bf16_bits(v) : to_f16_bits(v);
+                        const float r = S.storage == 1 ? bf16_bits_to_float(hb[q]) : f16_bits_to_float(hb[q]);
+                        norm = fmaf(r, r, norm);
+                    }
+                    hdst[(int64_t)c * S.C] = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16),
+                                                        hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
+                }
+            }
+        }
+        __syncthreads();   // the next piece takes the rows' place
     }
     if (lane < cnt) {
         const uint32_t g = (uint32_t)slab * (uint32_t)S.C + (uint32_t)slot;
-        const float *row = reinterpret_cast<const float *>(srow + lane * ld);
-        if (S.storage == 0) {
-            float n32 = 0.f;   // fp32 squared norm, sequential over ascending dimensions
-            for (int j = 0; j < 4 * dp4; j++) n32 = fmaf(row[j], row[j], n32);
-            S.xnorm[g] = n32;
-        } else {
-            // reduced-precision copy (round to nearest even), 8 dims per chunk,
-            // and the fp32 squared norm of the rounded row (L2 scan epilogue)
-            uint4 *hdst = S.hdata + (int64_t)slab * S.dp8 * S.C + slot;
-            float nrm = 0.f;
-            for (int c = 0; c < S.dp8; c++) {
-                uint32_t hb[8];
-#pragma unroll
-                for (int q = 0; q < 8; q++) {
-                    const int j = 8 * c + q;
-                    const float v = j < S.d ? row[j] : 0.f;
-                    hb[q] = S.storage == 1 ? to_bf16_bits(v) : to_f16_bits(v);
-                    const float r = S.storage == 1 ? bf16_bits_to_float(hb[q]) : f16_bits_to_float(hb[q]);
-                    nrm = fmaf(r, r, nrm);
-                }
-                hdst[(int64_t)c * S.C] = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16),
-                                                    hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
-            }
-            if (S.xnorm) S.xnorm[g] = nrm;
-        }
+        if (S.xnorm) S.xnorm[g] = norm;
         const int64_t u = ids[i];
         S.sids[g] = (uint32_t)u;
         S.att[u] = g;
@@ -945,16 +946,11 @@ void launch_add_alloc(hipStream_t st, const Dev &S) {
 void launch_add_scatter(hipStream_t st, const Dev &S, int n, const float *x, const int64_t *ids, const Batch &B) {
     // B.rec (free during an add once its upsert deletes are done) takes each entry's destination slot
     hipLaunchKernelGGL(k_add_inv, dim3(blocks(n)), dim3(256), 0, st, S, n, B.assign, B.rank, B.inv, B.rec);
-    const bool vec = (S.d % 4 == 0) && (((uintptr_t)x & 15) == 0);
-    if (vec && S.dp4 <= 64)
+    if ((S.d % 4 == 0) && (((uintptr_t)x & 15) == 0))
         hipLaunchKernelGGL(k_add_scatter_lds, dim3(blocks(n, SENT)), dim3(64),
-                           (size_t)SENT * (S.dp4 + 1) * sizeof(float4), st, S, x, ids, B.inv, B.rec);
-    else if (vec)
-        hipLaunchKernelGGL(k_add_scatter<true>, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank,
-                           B.inv);
+                           (size_t)SENT * ((S.dp4 < SCH ? S.dp4 : SCH) + 1) * sizeof(float4), st, S, x, ids, B.inv, B.rec);
     else
-        hipLaunchKernelGGL(k_add_scatter<false>, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank,
-                           B.inv);
+        hipLaunchKernelGGL(k_add_scatter, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank, B.inv);
 }
 
 void launch_add_cleanup(hipStream_t st, const Dev &S, int n, const int64_t *ids) {
