@@ -218,8 +218,9 @@ __global__ __launch_bounds__(256) void k_add_inv(Dev S, int n, const int32_t *__
 
 // One lane per new entry, in entry order: consecutive lanes fill consecutive
 // slots of a list, so each 16-byte dimension chunk of 64 entries is one
-// contiguous KiB write; the lane reads its source row in order.  For rows whose
-// length or address does not allow 16-byte reads.
+// contiguous KiB write; the lane reads its source row in order (VEC: 16 bytes at a
+// time).
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restrict__ x,
                                                      const int64_t *__restrict__ ids,
                                                      const int32_t *__restrict__ assign,
@@ -238,11 +239,15 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
     float n32 = 0.f;   // fp32 squared norm (fp32 storage)
     for (int c = 0; c < S.dp4; c++) {
         float4 v;
-        const int j = 4 * c;
-        v.x = j < S.d ? xr[j] : 0.f;
-        v.y = j + 1 < S.d ? xr[j + 1] : 0.f;
-        v.z = j + 2 < S.d ? xr[j + 2] : 0.f;
-        v.w = j + 3 < S.d ? xr[j + 3] : 0.f;
+        if (VEC) {
+            v = reinterpret_cast<const float4 *>(xr)[c];
+        } else {
+            const int j = 4 * c;
+            v.x = j < S.d ? xr[j] : 0.f;
+            v.y = j + 1 < S.d ? xr[j + 1] : 0.f;
+            v.z = j + 2 < S.d ? xr[j + 2] : 0.f;
+            v.w = j + 3 < S.d ? xr[j + 3] : 0.f;
+        }
         dst[(int64_t)c * S.C] = v;
         n32 = fmaf(v.x, v.x, n32);
         n32 = fmaf(v.y, v.y, n32);
@@ -286,9 +291,14 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
 // consecutive slots), so reads and writes are both contiguous runs.  16
 // entries per wave keep the staging area at 8.25 KiB (d = 128), so that many
 // waves per CU have loads in flight.  Rows of more than SCH chunks go through in pieces
-// of SCH: one lane per row left 5,000 rows of 960 values on 20 blocks (58 us).
-constexpr int SENT = 16, SCH = 64;
+// of SCH, one after the other, so a wave takes 4 of them: 5,000 rows of 960 values
+// 58 us with a lane per row (20 blocks), 36 with 16 rows per wave, 22 with 4.  Past
+// WIDE_STAGED of them a lane per row fills the chip and writes longer runs, and with lazy
+// deletes fences once per 64 rows: the insert of 50,000 rows of 960 values takes 286 us
+// (lazy 306) that way and 332 (786) with 4 rows per wave, of 5,000 171 (166) and 134 (137).
+constexpr int SCH = 64, WIDE_STAGED = 8192;
 
+template <int SENT>
 __global__ __launch_bounds__(64) void k_add_scatter_lds(Dev S, const float *__restrict__ x,
                                                          const int64_t *__restrict__ ids,
                                                          const int32_t *__restrict__ inv,
@@ -946,11 +956,17 @@ void launch_add_alloc(hipStream_t st, const Dev &S) {
 void launch_add_scatter(hipStream_t st, const Dev &S, int n, const float *x, const int64_t *ids, const Batch &B) {
     // B.rec (free during an add once its upsert deletes are done) takes each entry's destination slot
     hipLaunchKernelGGL(k_add_inv, dim3(blocks(n)), dim3(256), 0, st, S, n, B.assign, B.rank, B.inv, B.rec);
-    if ((S.d % 4 == 0) && (((uintptr_t)x & 15) == 0))
-        hipLaunchKernelGGL(k_add_scatter_lds, dim3(blocks(n, SENT)), dim3(64),
-                           (size_t)SENT * ((S.dp4 < SCH ? S.dp4 : SCH) + 1) * sizeof(float4), st, S, x, ids, B.inv, B.rec);
+    const auto staged = [&](auto kernel, int sent) {
+        hipLaunchKernelGGL(kernel, dim3(blocks(n, sent)), dim3(64),
+                           (size_t)sent * ((S.dp4 < SCH ? S.dp4 : SCH) + 1) * sizeof(float4), st, S, x, ids, B.inv, B.rec);
+    };
+    const bool vec = (S.d % 4 == 0) && (((uintptr_t)x & 15) == 0);
+    if (vec && S.dp4 <= SCH) staged(k_add_scatter_lds<16>, 16);
+    else if (vec && n <= WIDE_STAGED) staged(k_add_scatter_lds<4>, 4);
+    else if (vec)
+        hipLaunchKernelGGL(k_add_scatter<true>, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank, B.inv);
     else
-        hipLaunchKernelGGL(k_add_scatter, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank, B.inv);
+        hipLaunchKernelGGL(k_add_scatter<false>, dim3(blocks(n)), dim3(256), 0, st, S, x, ids, B.assign, B.rank, B.inv);
 }
 
 void launch_add_cleanup(hipStream_t st, const Dev &S, int n, const int64_t *ids) {

@@ -160,19 +160,19 @@ def test_compaction_slab_words(C):
         assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
 
 
-# rows staged in pieces of 64 chunks of 4 values: one whole piece, one and a remainder, several, and a last wave of
-# fewer than 16 entries
-@pytest.mark.parametrize("d,n", [(256, 16), (260, 17), (512, 33), (1028, 47)])
+# rows staged in pieces of 64 chunks of 4 values: one whole piece, one and a remainder, several, a last wave of fewer
+# entries than it holds, and either side of the batch from which wide rows are not staged
+@pytest.mark.parametrize("d,n", [(256, 16), (260, 17), (512, 33), (1028, 47), (260, 8192), (260, 8193)])
 def test_insert_wide_rows(d, n):
     rng = np.random.default_rng([26, d])
     cent = rng.standard_normal((5, d)).astype(np.float32)
     x = (cent[rng.integers(0, 5, n)] + 0.1 * rng.standard_normal((n, d))).astype(np.float32)
-    ix = sivf.Index(d, 5, cent, slab_capacity=8, num_slabs=n, id_capacity=n, max_batch=n, max_queries=n, max_k=8, max_nprobe=5)
+    ix = sivf.Index(d, 5, cent, slab_capacity=8, num_slabs=n, id_capacity=n, max_batch=n, max_queries=64, max_k=8, max_nprobe=5)
     ref = oracle.OracleIndex(d, 5, cent, 0, 8, n, n)
     ix.add(x, np.arange(n))
     assert ix.sync() == 0 and ref.add(x, np.arange(n)) == 0
     np.testing.assert_array_equal(ix.get_rows(np.arange(n)).cpu().numpy(), x)
-    gd, gl = ix.search(x, 8, 5)
+    gd, gl = ix.search(x[-64:], 8, 5)
     assert ix.sync() == 0
-    st, rd, rl = ref.search(x, 8, 5)
+    st, rd, rl = ref.search(x[-64:], 8, 5)
     assert st == 0 and compare_results(gd.cpu().numpy(), gl.cpu().numpy(), rd, rl) == 0
