@@ -71,7 +71,7 @@ typedef enum { SIVF_F32 = 0, SIVF_BF16 = 1, SIVF_F16 = 2 } sivf_dtype;
  *  SIVF_DELETE_LAZY: the paper's eviction (Sec. 3.4, Alg. 4): a validity bit
  *    per slot is cleared with an atomic AND (the 1 -> 0 transition counts the
  *    removal exactly once, Theorem 3) and nothing moves, so a delete never
- *    waits for searches; inserts publish their slots with a release fence and
+ *    waits for searches; inserts publish their slots once they are written, with
  *    an atomic OR (Alg. 2).  Dead slots keep their space until
  *    sivf_compact. */
 typedef enum { SIVF_DELETE_COMPACT = 0, SIVF_DELETE_LAZY = 1 } sivf_delete_mode;

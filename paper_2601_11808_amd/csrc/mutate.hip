@@ -33,16 +33,6 @@ namespace sivf {
 
 __device__ __forceinline__ int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// Lazy deletes: make a written slot visible (the paper's Alg. 2): a release
-// fence at agent scope orders the slot's payload, id and address-table writes
-// before the atomic OR that sets its validity bit, so a reader that sees the
-// bit (on any XCD) sees the entry.
-__device__ __forceinline__ void publish_slot(const Dev &S, int slab, int slot) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_or(S.bits + (int64_t)slab * S.bw + (slot >> 6), 1ull << (slot & 63), __ATOMIC_RELAXED,
-                          __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // ------------------------------------------------------------------ insert
 
 __global__ __launch_bounds__(256) void k_add_prepare(Dev S, int n, const int64_t *__restrict__ ids) {
@@ -281,7 +271,6 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
         S.sids[g] = (uint32_t)u;
         S.att[u] = g;
     }
-    if (S.bits) publish_slot(S, slab, slot);
 }
 
 // LDS-staged form of the scatter (16-byte aligned rows of whole chunks):
@@ -293,9 +282,9 @@ __global__ __launch_bounds__(256) void k_add_scatter(Dev S, const float *__restr
 // waves per CU have loads in flight.  Rows of more than SCH chunks go through in pieces
 // of SCH, one after the other, so a wave takes 4 of them: 5,000 rows of 960 values
 // 58 us with a lane per row (20 blocks), 36 with 16 rows per wave, 22 with 4.  Past
-// WIDE_STAGED of them a lane per row fills the chip and writes longer runs, and with lazy
-// deletes fences once per 64 rows: the insert of 50,000 rows of 960 values takes 286 us
-// (lazy 306) that way and 332 (786) with 4 rows per wave, of 5,000 171 (166) and 134 (137).
+// WIDE_STAGED of them a lane per row fills the chip and writes longer runs: the insert of
+// 50,000 rows of 960 values takes 286 us that way and 332 with 4 rows per wave, of
+// 5,000 171 and 134.
 constexpr int SCH = 64, WIDE_STAGED = 8192;
 
 template <int SENT>
@@ -381,15 +370,26 @@ __global__ __launch_bounds__(64) void k_add_scatter_lds(Dev S, const float *__re
         const int64_t u = ids[i];
         S.sids[g] = (uint32_t)u;
         S.att[u] = g;
-        if (S.bits) publish_slot(S, slab, slot);
     }
 }
 
+// Clears the batch's marks and, with lazy deletes, makes the written slots visible (the
+// paper's Alg. 2): the end of the scatter's launch is the release that orders every
+// slot's payload, id and address-table writes before the atomic OR that sets its
+// validity bit, so a reader that sees the bit (on any XCD) sees the entry.  (A fence in
+// every wave of the scatter writes its XCD's L2 back each time: the insert of 50,000 rows
+// of 960 values took 309 us and takes 283.)  Equal ids of a batch set the same bit.
 __global__ __launch_bounds__(256) void k_add_cleanup(Dev S, int n, const int64_t *__restrict__ ids) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const int64_t u = ids[i];
-    if (u >= 0 && u < S.id_capacity) S.mark[u] = -1;
+    if (u < 0 || u >= S.id_capacity) return;
+    S.mark[u] = -1;
+    if (S.bits && !call_failed(S.ctl)) {
+        const uint32_t g = S.att[u], slot = g % (uint32_t)S.C;
+        __hip_atomic_fetch_or(S.bits + (int64_t)(g / (uint32_t)S.C) * S.bw + (slot >> 6), 1ull << (slot & 63),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // ------------------------------------------------------------------ delete
